@@ -82,19 +82,21 @@ struct EncGeom {
 constexpr int kEncCols = 16;     // columns per output tile: 128-byte row segments
 constexpr int kOtRow = kEncCols + 1;   // LDS words per tile row (odd: no bank conflicts)
 
-// This lane's kDw pixel dwords (features f0 .. f0 + 4*kDw - 1 of sample s);
-// zero past the batch or past the last feature.  `full` (wave-uniform): the
-// whole column is inside the batch, the tile holds kFT features and rows are
-// dword aligned, so the loads need no guards.
-template <int kDw>
-__device__ __forceinline__ void load_pixels(const uint8_t *__restrict__ x, int64_t s, int64_t n,
-                                            int32_t d, int f0, int nf, int aligned4, bool full,
-                                            uint32_t (&px)[kDw])
+// A dword at any address (gfx950 global loads need no alignment).
+__device__ __forceinline__ uint32_t load_u32(const uint8_t *p)
 {
-    const uint8_t *row = x + s * d + f0;
+    uint32_t v;
+    __builtin_memcpy(&v, p, sizeof v);
+    return v;
+}
+
+// kDw dwords from a row of pixels.  vec16 (wave-uniform): 16-byte aligned.
+template <int kDw>
+__device__ __forceinline__ void load_row(const uint8_t *__restrict__ row, int vec16,
+                                         uint32_t (&px)[kDw])
+{
     if constexpr (kDw % 4 == 0) {
-        // tiles of whole 16-byte pieces in 16-byte aligned rows (aligned4 == 2)
-        if (full && aligned4 == 2) {
+        if (vec16) {
 #pragma unroll
             for (int q = 0; q < kDw / 4; ++q) {
                 const u32x4 v = reinterpret_cast<const u32x4 *>(row)[q];
@@ -106,28 +108,45 @@ __device__ __forceinline__ void load_pixels(const uint8_t *__restrict__ x, int64
             return;
         }
     }
-    if (full) {
+#pragma unroll
+    for (int q = 0; q < kDw; ++q)
+        px[q] = load_u32(row + 4 * q);
+}
+
+// This lane's kDw pixel dwords (features f0 .. f0 + 4*kDw - 1 of sample s);
+// zero past the batch or past the nf features of the tile.  full and inside
+// are wave-uniform: the tile holds 4*kDw features; the column's 64 samples are
+// all in the batch.
+template <int kDw>
+__device__ __forceinline__ void load_pixels(const uint8_t *__restrict__ x, int64_t s, int64_t n,
+                                            int32_t d, int f0, int nf, int vec16, bool full,
+                                            bool inside, uint32_t (&px)[kDw])
+{
+    if (full && inside) {
+        load_row<kDw>(x + s * d + f0, vec16, px);
+    } else if (full) {
+        load_row<kDw>(x + min(s, n - 1) * d + f0, vec16, px);
 #pragma unroll
         for (int q = 0; q < kDw; ++q)
-            px[q] = reinterpret_cast<const uint32_t *>(row)[q];
-    } else if (s < n && aligned4) {
-#pragma unroll
-        for (int q = 0; q < kDw; ++q)
-            px[q] = (4 * q < nf) ? reinterpret_cast<const uint32_t *>(row)[q] : 0u;
-    } else if (s < n) {
+            px[q] = s < n ? px[q] : 0u;
+    } else {
+        // rows shorter than a tile
+        const uint8_t *row = x + s * d + f0;
 #pragma unroll
         for (int q = 0; q < kDw; ++q) {
             uint32_t v = 0;
+            if (s < n) {
+                if (4 * q + 4 <= nf) {
+                    v = load_u32(row + 4 * q);
+                } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (4 * q + u < nf)
-                    v |= (uint32_t)row[4 * q + u] << (8 * u);
+                    for (int u = 0; u < 4; ++u)
+                        if (4 * q + u < nf)
+                            v |= (uint32_t)row[4 * q + u] << (8 * u);
+                }
+            }
             px[q] = v;
         }
-    } else {
-#pragma unroll
-        for (int q = 0; q < kDw; ++q)
-            px[q] = 0;
     }
 }
 
@@ -135,7 +154,7 @@ template <int B, int LAYOUT, int CS>
 __global__ __launch_bounds__(kThreads) void k_encode_t(
     const uint8_t *__restrict__ x, int64_t n, int32_t d, const uint8_t *__restrict__ th,
     uint64_t *__restrict__ out, int64_t W, int64_t W_cols, int32_t n_ftiles,
-    int32_t tiles_per_block, int64_t n_tiles, int64_t n_tgroups, int aligned4, int kind)
+    int32_t tiles_per_block, int64_t n_tiles, int64_t n_tgroups, int vec16, int kind)
 {
     using G = EncGeom<B>;
     constexpr int kWires = G::kG * G::kWPG;              // wire rows of one output tile
@@ -149,7 +168,15 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
     const int ft = (int)(loc % n_ftiles);
     if (tg >= n_tgroups)
         return;
-    const int f0 = ft * G::kFT;
+    // the last tile of rows that are no whole number of tiles starts earlier
+    // and repeats `skip` features of the one before, which it does not write:
+    // every tile's loads are then whole and rows need no alignment.  Loads
+    // guarded per dword (per byte in rows that are not whole dwords) went out
+    // one by one: 99991 x 3071 pixels at b = 3 took 1071 us against 207,
+    // 50021 x 1021 at b = 6 185 against 42, 100000 x 3060 at b = 3 154
+    // against 145; rows of whole 16-byte pieces and tiles are as they were
+    const int f0 = max(min(ft * G::kFT, d - G::kFT), 0);
+    const int skip = ft * G::kFT - f0;
     const int nf = min(G::kFT, d - f0);
     const int64_t D0 = (int64_t)d * B;
     const int lane = threadIdx.x % kWave;
@@ -197,13 +224,13 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
     const int c_first = part * cpb + wave * cpw;      // this wave's first column of a tile
     const int64_t t0 = (tg / CS) * tiles_per_block;
     const int64_t t1 = min(t0 + tiles_per_block, n_tiles);
-    // columns whose 64 samples are all in the batch, in a full aligned tile
-    const bool tile_full = aligned4 && nf == G::kFT;
-    auto col_full = [&](int64_t gcol) { return tile_full && (gcol + 1) * kWave <= n; };
+    const bool full = nf == G::kFT;
+    auto inside = [&](int64_t gcol) { return (gcol + 1) * kWave <= n; };
     uint32_t px[G::kDw];
     {
         const int64_t gcol = t0 * kEncCols + c_first;
-        load_pixels<G::kDw>(x, gcol * kWave + lane, n, d, f0, nf, aligned4, col_full(gcol), px);
+        load_pixels<G::kDw>(x, gcol * kWave + lane, n, d, f0, nf, vec16, full, inside(gcol),
+                            px);
     }
     for (int64_t tile = t0; tile < t1; ++tile) {
         for (int cw = 0; cw < cpw; ++cw) {
@@ -214,8 +241,8 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
             if (more) {
                 const int64_t ncol = (cw + 1 < cpw) ? tile * kEncCols + col + 1
                                                     : (tile + 1) * kEncCols + c_first;
-                load_pixels<G::kDw>(x, ncol * kWave + lane, n, d, f0, nf, aligned4, col_full(ncol),
-                                    nx);
+                load_pixels<G::kDw>(x, ncol * kWave + lane, n, d, f0, nf, vec16, full,
+                                    inside(ncol), nx);
             }
 #pragma unroll
             for (int gi = 0; gi < G::kG; ++gi) {
@@ -254,7 +281,7 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
             const int gi = r / G::kWPG, p = r % G::kWPG;
             const int fg = gi * G::kFPG + p / B;           // feature of this wire in the tile
             const int64_t wb = wb0 + c2;
-            if (fg >= nf || wb >= W_cols)
+            if (fg < skip || fg >= nf || wb >= W_cols)
                 continue;
             const int64_t wire = (int64_t)(f0 + gi * G::kFPG) * B + p;
             const uint64_t w0 = otile[r * kOtRow + c2], w1 = otile[r * kOtRow + c2 + 1];
@@ -388,22 +415,19 @@ hipError_t launch_t(const uint8_t *x, int64_t n, int32_t d, const uint8_t *th, u
     const int64_t blocks = n_tg_pad * n_ftiles;
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
-    // 2: rows 16-byte aligned, 1: 4-byte aligned, 0: neither
-    const int aligned4 = ((d % 16 == 0) && ((uintptr_t)x % 16 == 0))  ? 2
-                         : ((d % 4 == 0) && ((uintptr_t)x % 4 == 0)) ? 1
-                                                                      : 0;
+    const int vec16 = (d % 16 == 0) && ((uintptr_t)x % 16 == 0);
     if (csplit == 4)
         hipLaunchKernelGGL((k_encode_t<B, LAYOUT, 4>), dim3((unsigned)blocks), dim3(kThreads), 0,
                            stream, x, n, d, th, out, W, W_cols, n_ftiles, (int32_t)tpb, n_tiles,
-                           n_tg, aligned4, kind);
+                           n_tg, vec16, kind);
     else if (csplit == 2)
         hipLaunchKernelGGL((k_encode_t<B, LAYOUT, 2>), dim3((unsigned)blocks), dim3(kThreads), 0,
                            stream, x, n, d, th, out, W, W_cols, n_ftiles, (int32_t)tpb, n_tiles,
-                           n_tg, aligned4, kind);
+                           n_tg, vec16, kind);
     else
         hipLaunchKernelGGL((k_encode_t<B, LAYOUT, 1>), dim3((unsigned)blocks), dim3(kThreads), 0,
                            stream, x, n, d, th, out, W, W_cols, n_ftiles, (int32_t)tpb, n_tiles,
-                           n_tg, aligned4, kind);
+                           n_tg, vec16, kind);
     return hipGetLastError();
 }
 
