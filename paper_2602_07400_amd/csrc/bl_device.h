@@ -17,6 +17,13 @@
 #define BL_MUX_BITOP3 1
 #endif
 
+// v_writelane_b32 as the compiler's own intrinsic (clang has no builtin for
+// it): old with lane `lane` replaced by the wave-uniform value.  In inline asm
+// the wait states between a compare that writes the value's SGPR and the
+// v_writelane that reads it are not inserted.
+extern "C" __device__ int bl_writelane(int value, int lane, int old)
+    __asm("llvm.amdgcn.writelane.i32");
+
 namespace bl {
 namespace dev {
 

@@ -303,17 +303,6 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
     }
 }
 
-// Write a wave-uniform value into one lane of a VGPR (v_writelane_b32).  The
-// lane select goes through M0: with the value already in an SGPR, a second
-// SGPR operand would exceed the one-SGPR constant-bus limit of GFX9-family
-// VOP3 encodings.
-__device__ __forceinline__ uint32_t write_lane(uint32_t acc, uint32_t value, int lane)
-{
-    asm("s_mov_b32 m0, %2\n\tv_writelane_b32 %0, %1, m0"
-        : "+v"(acc) : "s"(value), "s"(lane) : "m0");
-    return acc;
-}
-
 constexpr int kBFeat = 32;             // features per tile
 constexpr int kBRow = kBFeat + 4;      // LDS bytes per staged sample row (9 dwords)
 constexpr int kBCols = 16;             // 64-sample columns per tile
@@ -375,8 +364,8 @@ __global__ __launch_bounds__(kThreads) void k_encode_ballot(
             for (int t = 0; t < b; ++t, ++q) {
                 const uint64_t m = __ballot(xv > (uint32_t)ths[f * b + t]);
                 const int pos = q & (kWave - 1);
-                acc_lo = write_lane(acc_lo, (uint32_t)m, pos);
-                acc_hi = write_lane(acc_hi, (uint32_t)(m >> 32), pos);
+                acc_lo = (uint32_t)bl_writelane((int)(uint32_t)m, pos, (int)acc_lo);
+                acc_hi = (uint32_t)bl_writelane((int)(uint32_t)(m >> 32), pos, (int)acc_hi);
                 if (pos == kWave - 1) {
                     const int64_t wire = wire0 + (q - (kWave - 1)) + lane;
                     out[out_index<LAYOUT>(wire, col, W, D0)] = ((uint64_t)acc_hi << 32) | acc_lo;
