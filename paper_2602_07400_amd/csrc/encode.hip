@@ -162,11 +162,8 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
     __shared__ uint8_t ths[G::kFT * B];
     __shared__ uint64_t otile[kWires * kOtRow];
 
-    const int bid = blockIdx.x;
-    const int64_t loc = local_of(bid);
-    const int64_t tg = (int64_t)xcd_of(bid) + (int64_t)kXcds * (loc / n_ftiles);
-    const int ft = (int)(loc % n_ftiles);
-    if (tg >= n_tgroups)
+    int tg, ft;
+    if (!dealt_task(blockIdx.x, (int)n_tgroups, n_ftiles, tg, ft))
         return;
     // the last tile of rows that are no whole number of tiles starts earlier
     // and repeats `skip` features of the one before, which it does not write:
@@ -220,9 +217,9 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
     constexpr int cpb = kEncCols / CS;
     constexpr int cpw = cpb / (kThreads / kWave);
     static_assert(cpw >= 1, "at least one column per wave");
-    const int part = (int)(tg % CS);
+    const int part = tg % CS;
     const int c_first = part * cpb + wave * cpw;      // this wave's first column of a tile
-    const int64_t t0 = (tg / CS) * tiles_per_block;
+    const int64_t t0 = (int64_t)(tg / CS) * tiles_per_block;
     const int64_t t1 = min(t0 + tiles_per_block, n_tiles);
     const bool full = nf == G::kFT;
     auto inside = [&](int64_t gcol) { return (gcol + 1) * kWave <= n; };
@@ -317,15 +314,12 @@ __global__ __launch_bounds__(kThreads) void k_encode_ballot(
     __shared__ uint8_t xs[kBSamples * kBRow];
     __shared__ uint8_t ths[kBFeat * 64];
 
-    const int bid = blockIdx.x;
-    const int64_t loc = local_of(bid);
-    const int64_t cg = (int64_t)xcd_of(bid) + (int64_t)kXcds * (loc / n_ftiles);
-    const int ft = (int)(loc % n_ftiles);
-    if (cg >= n_cgroups)
+    int cg, ft;
+    if (!dealt_task(blockIdx.x, (int)n_cgroups, n_ftiles, cg, ft))
         return;
     const int f0 = ft * kBFeat;
     const int nf = min(kBFeat, d - f0);
-    const int64_t s0 = cg * kBSamples;
+    const int64_t s0 = (int64_t)cg * kBSamples;
     const int64_t D0 = (int64_t)d * b;
 
     for (int q = threadIdx.x; q < nf * b; q += kThreads)
@@ -353,7 +347,7 @@ __global__ __launch_bounds__(kThreads) void k_encode_ballot(
     const int nwires = nf * b;
     const int64_t wire0 = (int64_t)f0 * b;
     for (int c = wave; c < kBCols; c += kThreads / kWave) {
-        const int64_t col = cg * kBCols + c;
+        const int64_t col = (int64_t)cg * kBCols + c;
         if (col >= W_cols)
             break;
         const uint8_t *xrow = &xs[(c * kWave + lane) * kBRow];
@@ -400,8 +394,7 @@ hipError_t launch_t(const uint8_t *x, int64_t n, int32_t d, const uint8_t *th, u
     while (csplit < 4 && n_tiles * n_ftiles * csplit < 1024)
         csplit *= 2;
     const int64_t n_tg = (n_tiles + tpb - 1) / tpb * csplit;
-    const int64_t n_tg_pad = (n_tg + kXcds - 1) / kXcds * kXcds;
-    const int64_t blocks = n_tg_pad * n_ftiles;
+    const int64_t blocks = dealt_blocks(n_tg, n_ftiles);
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     const int vec16 = (d % 16 == 0) && ((uintptr_t)x % 16 == 0);
@@ -427,8 +420,7 @@ hipError_t launch_ballot(const uint8_t *x, int64_t n, int32_t d, const uint8_t *
     const int64_t W = (n + 63) / 64;
     const int32_t n_ftiles = (d + kBFeat - 1) / kBFeat;
     const int64_t n_cg = (W_cols + kBCols - 1) / kBCols;
-    const int64_t n_cg_pad = (n_cg + kXcds - 1) / kXcds * kXcds;
-    const int64_t blocks = n_cg_pad * n_ftiles;
+    const int64_t blocks = dealt_blocks(n_cg, n_ftiles);
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     const bool aligned4 = (d % 4 == 0) && ((uintptr_t)x % 4 == 0);

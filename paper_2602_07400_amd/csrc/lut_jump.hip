@@ -170,11 +170,8 @@ __global__ __launch_bounds__(kJumpThreads) void k_jump_layer(
     int32_t w_out, uint64_t *__restrict__ out, int32_t n_nblk, int32_t n_pairs)
 {
     constexpr int kRow = kSlabWords * 8;          // bytes of one row segment
-    const int bid = blockIdx.x;
-    const int loc = local_of(bid);
-    const int pair = (loc / n_nblk) * kXcds + xcd_of(bid);
-    const int nblk = loc % n_nblk;
-    if (pair >= n_pairs)
+    int pair, nblk;
+    if (!dealt_task(blockIdx.x, n_pairs, n_nblk, pair, nblk))
         return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
@@ -308,7 +305,7 @@ hipError_t launch_jump_layer(const uint64_t *in, int32_t w_in, int64_t n_slabs,
         return e;
     const int64_t n_pairs = n_slabs / 2;
     const int32_t n_nblk = (w_out + kJumpNodesPerBlock - 1) / kJumpNodesPerBlock;
-    const int64_t blocks = (n_pairs + kXcds - 1) / kXcds * kXcds * n_nblk;
+    const int64_t blocks = dealt_blocks(n_pairs, n_nblk);
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_jump_layer, dim3((unsigned)blocks), dim3(kJumpThreads), 0, stream, in,

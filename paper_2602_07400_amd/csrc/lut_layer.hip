@@ -56,12 +56,10 @@ __global__ __launch_bounds__(kThreads) void k_lut_layer(
     __shared__ int32_t s_conn[NB * K];
     __shared__ uint64_t s_tab[NB];
 
-    const int bid = blockIdx.x;
-    const int loc = local_of(bid);
-    const int win = win_base + (loc / n_nblk) * kXcds + xcd_of(bid);
-    const int nblk = loc % n_nblk;
-    if (win >= n_win)
+    int win, nblk;
+    if (!dealt_task(blockIdx.x, n_win - win_base, n_nblk, win, nblk))
         return;
+    win += win_base;
     const int node0 = nblk * NB;
     const int nodes = min(NB, w_out - node0);
 
@@ -449,11 +447,8 @@ __global__ __launch_bounds__(kThreads, BL_LUT_MINWAVES) void k_lut_slab(
     __shared__ uint64_t s_tab[NB];
     __shared__ int s_kp[SPEC ? kPasses + 2 : 1];
 
-    const int bid = blockIdx.x;
-    const int loc = local_of(bid);
-    const int slab = (loc / n_nblk) * kXcds + xcd_of(bid);
-    const int nblk = loc % n_nblk;
-    if (slab >= n_slabs)
+    int slab, nblk;
+    if (!dealt_task(blockIdx.x, n_slabs, n_nblk, slab, nblk))
         return;
     const int node0 = nblk * NB;
     const int nodes = min(NB, w_out - node0);
@@ -562,8 +557,7 @@ hipError_t launch_slab_kn(const uint64_t *in, int32_t w_in, int64_t n_slabs,
                           uint64_t *out, const uint8_t *fanin, hipStream_t stream)
 {
     const int32_t n_nblk = (w_out + NB - 1) / NB;
-    const int64_t slabs_pad = (n_slabs + kXcds - 1) / kXcds * kXcds;
-    const int64_t blocks = slabs_pad * n_nblk;
+    const int64_t blocks = dealt_blocks(n_slabs, n_nblk);
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     if (fanin)
@@ -790,11 +784,8 @@ __global__ __launch_bounds__(kThreads, (head_min_waves<K, SPEC>())) void k_lut_s
     static_assert(kHeadMaxPasses <= kWave, "a lane per pass stages the fan-ins");
     __shared__ int s_kp[SPEC ? kHeadMaxPasses + 2 : 1];
 
-    const int bid = blockIdx.x;
-    const int loc = local_of(bid);
-    const int slab = (loc / n_nblk) * kXcds + xcd_of(bid);
-    const int nblk = loc % n_nblk;
-    if (slab >= n_slabs)
+    int slab, nblk;
+    if (!dealt_task(blockIdx.x, n_slabs, n_nblk, slab, nblk))
         return;
     const int cls = nblk / splits;               // one class per block
     const int split = nblk % splits;
@@ -936,8 +927,7 @@ hipError_t launch_slab_head_kp(const uint64_t *in, int32_t w_in, int64_t n_slabs
         return hipErrorInvalidValue;
     const int32_t splits = (g + nb - 1) / nb;
     const int64_t n_nblk = (int64_t)c * splits;
-    const int64_t slabs_pad = (n_slabs + kXcds - 1) / kXcds * kXcds;
-    const int64_t blocks = slabs_pad * n_nblk;
+    const int64_t blocks = dealt_blocks(n_slabs, n_nblk);
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     if (fanin)
@@ -977,9 +967,7 @@ hipError_t launch_mode(const uint64_t *in, int64_t W, const int32_t *conn,
                        int64_t win_base, int64_t n_win, hipStream_t stream)
 {
     const int32_t n_nblk = (w_out + kNB - 1) / kNB;
-    const int64_t span = n_win - win_base;
-    const int64_t span_pad = (span + kXcds - 1) / kXcds * kXcds;
-    const int64_t blocks = span_pad * n_nblk;
+    const int64_t blocks = dealt_blocks(n_win - win_base, n_nblk);
     if (blocks > 0x7fffffff || n_win > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((k_lut_layer<K, kLPN, kR, kNB, MODE>), dim3((unsigned)blocks),
