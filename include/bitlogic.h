@@ -66,7 +66,8 @@
  * - Entry points are thread-safe; calls on one stream run in order.
  *
  * ---------------------------------------------------- environment switches
- * Read at every forward call; it changes which kernels run, never results.
+ * Read at every forward call; they change which kernels run, never results.
+ * With either one set, small batches too run on the slab kernels.
  *   BITLOGIC_UNFUSED_HEAD=1   the forward stores the last layer's bits and
  *                             runs the separate head kernels instead of the
  *                             last layer fused with the GroupSum counting.
@@ -152,7 +153,10 @@ size_t bitlogic_forward_workspace_bytes(int64_t n_samples, int32_t n_features,
                                         int32_t n_layers, int32_t n_classes);
 
 /* How bitlogic_forward runs a network of this shape (host only, no HIP
- * call, nothing enqueued).  Fills *info and returns BITLOGIC_OK, or returns
+ * call, nothing enqueued).  It describes the slab kernels; small batches (of
+ * networks of two and more layers and up to 8 wires a feature, without an
+ * environment switch set) run by 64-sample columns in the same workspace, with
+ * the same results.  Fills *info and returns BITLOGIC_OK, or returns
  * the status bitlogic_forward would return for these sizes and descriptors
  * (info untouched).  Device pointers in `layers` are not dereferenced. */
 typedef struct bitlogic_forward_info {

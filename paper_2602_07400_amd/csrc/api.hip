@@ -139,11 +139,27 @@ struct ForwardPlan {
     bool fused;            // last layer + head in one kernel
     uint64_t jump_mask;    // bit l: layer l runs on the node-per-wave kernel
     size_t off_rec;        // its per-node records (shared by those layers)
+    bl::ColumnHeadPlan cols;   // cols.ok: the column kernels run the batch
 };
 
 bitlogic_network legacy_net(int32_t n_features, const uint8_t *thresholds, int32_t n_thresholds,
                             const bitlogic_layer *layers, int32_t n_layers, int32_t n_classes,
                             const int8_t *dsp_weights);
+
+// Work of a forward by columns, in units of about 4 ps of the whole GPU: a
+// wire, and a node of up to 4 or of 5 and 6 inputs.  The slab kernels take over
+// at kColumnMaxCost, where 30 random networks (1000 to 57000 nodes a layer, 64
+// to 33000 samples) crossed: columns against slabs 25.7 us : 29.7 at 2.7M,
+// 16.3 : 22.2 at 1.2M, 38.2 : 64.7 at 0.9M, but 32.0 : 30.2 at 3.5M, 45.9 :
+// 35.7 at 4.0M, 39.0 : 33.2 at 5.8M and 66.8 : 49.3 at 7.9M.
+constexpr int64_t kColumnMaxCost = 3000000;
+int64_t column_cost(int64_t W, int64_t wires, const bitlogic_layer *layers, int32_t L)
+{
+    int64_t per_column = wires;
+    for (int32_t l = 0; l < L; ++l)
+        per_column += (int64_t)layers[l].w_out * (layers[l].k <= 4 ? 2 : 5);
+    return W * per_column;
+}
 
 int plan_forward(int64_t n, int32_t d, int32_t b, const bitlogic_layer *layers, int32_t L,
                  int32_t c, const uint8_t *const *pass_fanin, ForwardPlan *fp)
@@ -214,6 +230,16 @@ int plan_forward(int64_t n, int32_t d, int32_t b, const bitlogic_layer *layers, 
         }
         w_in = layers[l].w_out;
     }
+    // small batches run by 64-sample columns, in the space of the slab layout's
+    // tensors (a column tensor is never larger): the encoded bits and the
+    // activations where the slab layout has them, counts that the caller does
+    // not receive over the encoded bits, which layer 0 has consumed by then.
+    // Where a switch asks for other kernels, or the encoder has more wires a
+    // feature than the column encoder's waves hold, the slab kernels run.
+    fp->cols = bl::plan_column_head(L >= 2 ? layers[L - 2].w_out : d * b, w_last, c);
+    fp->cols.ok = fp->cols.ok && L >= 2 && b <= 8 && fp->fused && jm == kJumpAuto &&
+                  (size_t)n * c * sizeof(int32_t) <= enc &&
+                  column_cost(fp->W, d * b, layers, L) <= kColumnMaxCost;
     fp->off_rec = fp->off_head + round_up(fp->head.ws_bytes);
     fp->total = fp->off_rec + (fp->jump_mask ? round_up(bl::jump_records_bytes(rec_w)) : 0);
     return BITLOGIC_OK;
@@ -349,6 +375,52 @@ int plan_network(const bitlogic_network *net, int64_t n, ForwardPlan *fp)
     return BITLOGIC_OK;
 }
 
+// The forward of a small batch by 64-sample columns (columns.hip).  mark(i)
+// records event i of the timed variant.
+template <class Mark>
+int forward_columns(const bitlogic_network *net, const ForwardPlan &fp, const uint8_t *x,
+                    int64_t n, int32_t *scores, int32_t *argmax, uint64_t *enc,
+                    uint64_t *const (&act)[2], hipStream_t s, Mark mark)
+{
+    const bitlogic_layer *layers = net->layers;
+    const int32_t L = net->n_layers, c = net->n_classes;
+    hipError_t e = mark(0);
+    if (e == hipSuccess)
+        e = bl::launch_column_encode(x, n, net->n_features, net->thresholds, net->n_bits, enc,
+                                     net->encoder == BITLOGIC_ENCODER_BINARY ? bl::kEncBinary
+                                                                             : bl::kEncThermometer,
+                                     s);
+    if (e == hipSuccess)
+        e = mark(1);
+    if (e != hipSuccess)
+        return hip_status(e, "forward: encode launch");
+    const uint64_t *cur = enc;
+    int32_t w_in = net->n_features * net->n_bits;
+    for (int32_t l = 0; l < L - 1; ++l) {
+        e = bl::launch_column_layer(cur, w_in, (int32_t)fp.W, layers[l].conn, layers[l].tables,
+                                    layers[l].w_out, layers[l].k, act[l & 1], s);
+        if (e == hipSuccess)
+            e = mark(2 + l);
+        if (e != hipSuccess)
+            return fail(BITLOGIC_ERR_HIP, "forward: layer %d launch: %s", l, hipGetErrorString(e));
+        cur = act[l & 1];
+        w_in = layers[l].w_out;
+    }
+    const bool dsp = net->head == BITLOGIC_HEAD_GROUPED_DSP;
+    // the counts: the caller's scores, or scratch where they are not wanted
+    int32_t *counts = !dsp && scores ? scores : reinterpret_cast<int32_t *>(enc);
+    e = bl::launch_column_head(cur, w_in, layers[L - 1].conn, layers[L - 1].tables,
+                               layers[L - 1].w_out, layers[L - 1].k, c, n, fp.cols, counts,
+                               dsp ? nullptr : argmax, s);
+    if (e == hipSuccess)
+        e = mark(L + 1);
+    if (e == hipSuccess && dsp)
+        e = bl::launch_grouped_dsp(counts, n, c, net->head_weights, scores, argmax, s);
+    if (e == hipSuccess)
+        e = mark(L + 2);
+    return hip_status(e, "forward: head launch");
+}
+
 int forward_impl(const bitlogic_network *net, const uint8_t *x, int64_t n_samples,
                  int32_t *scores, int32_t *argmax, void *workspace, size_t workspace_bytes,
                  void *stream, void *const *events, int32_t n_events)
@@ -391,6 +463,8 @@ int forward_impl(const bitlogic_network *net, const uint8_t *x, int64_t n_sample
     uint64_t *enc = reinterpret_cast<uint64_t *>(ws + fp.off_enc);
     uint64_t *act[2] = {reinterpret_cast<uint64_t *>(ws + fp.off_a),
                         reinterpret_cast<uint64_t *>(ws + fp.off_b)};
+    if (fp.cols.ok)
+        return forward_columns(net, fp, x, n_samples, scores, argmax, enc, act, s, mark);
     hipError_t e = mark(0);
     if (e == hipSuccess)
         e = bl::launch_encode(x, n_samples, net->n_features, net->thresholds, net->n_bits, enc,

@@ -183,6 +183,29 @@ hipError_t launch_grouped_dsp(const int32_t *counts, int64_t n, int32_t c,
                               const int8_t *weights, int32_t *logits, int32_t *argmax,
                               hipStream_t stream);
 
+// Small batches by 64-sample columns (columns.hip): packed tensors [W][rows].
+// plan_column_head: the classes of one head block (cpb, splits blocks a
+// column), whether it stages the column's rows in LDS, its LDS bytes, and
+// whether the column kernels can run it.
+constexpr size_t kColumnLds = 160 << 10;
+struct ColumnHeadPlan {
+    bool ok, staged;
+    int32_t cpb, splits;
+    size_t lds;
+};
+ColumnHeadPlan plan_column_head(int32_t w_in, int32_t w_out, int32_t c);
+hipError_t launch_column_encode(const uint8_t *x, int64_t n, int32_t d, const uint8_t *th,
+                                int32_t b, uint64_t *out, int kind, hipStream_t stream);
+hipError_t launch_column_layer(const uint64_t *in, int32_t w_in, int32_t W, const int32_t *conn,
+                               const uint64_t *tables, int32_t w_out, int32_t k, uint64_t *out,
+                               hipStream_t stream);
+// Last layer and GroupSum: counts int32 [n][c] (may be NULL if splits == 1) and
+// argmax (may be NULL).
+hipError_t launch_column_head(const uint64_t *in, int32_t w_in, const int32_t *conn,
+                              const uint64_t *tables, int32_t w_out, int32_t k, int32_t c,
+                              int64_t n, const ColumnHeadPlan &hp, int32_t *counts,
+                              int32_t *argmax, hipStream_t stream);
+
 // Peak probes (probes.hip): kProbeThreads = 256 lanes a block.
 hipError_t launch_probe_valu(uint32_t *out, int32_t blocks, int32_t iters, uint32_t seed,
                              hipStream_t stream);

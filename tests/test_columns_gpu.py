@@ -1,0 +1,100 @@
+"""Small batches, which run by 64-sample columns, against the oracle and against
+the slab kernels (an environment switch keeps those): one to many columns and
+nodes a lane, ragged batches, every encoder width and fan-in, heads whose
+classes sit in one block or several, groups smaller than a wave and larger than
+a block's rounds, inputs staged in LDS and not, and both class heads."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2602_07400_amd import bitlogic as bl
+from paper_2602_07400_amd.workloads import draw_connectivity
+
+pytestmark = pytest.mark.gpu
+
+DEV = torch.device("cuda:0")
+
+
+def check(monkeypatch, n, d, b, widths, k, c, dsp=False, binary=False, seed=0):
+    rng = np.random.default_rng([n, d, b, c, seed])
+    ks = [k] * len(widths) if isinstance(k, int) else list(k)
+    layers, w_in = [], d * b
+    for w, kk in zip(widths, ks):
+        # whole 64-bit tables: bits past 2^k are ignored
+        layers.append((draw_connectivity(rng, w, min(kk, w_in), w_in),
+                       rng.integers(0, 1 << 63, size=w, dtype=np.uint64) * np.uint64(2)
+                       + rng.integers(0, 2, size=w, dtype=np.uint64)))
+        w_in = w
+    x = rng.integers(0, 256, size=(n, d), dtype=np.uint8)
+    th = rng.integers(0, 256, size=(d, b), dtype=np.uint8)
+    q = rng.integers(-128, 128, size=(c, c)).astype(np.int8) if dsp else None
+    kw = dict(encoder="binary", n_features=d, n_bits=b) if binary else {}
+    model = bl.BitlogicModel.from_numpy(None if binary else th, layers, c, device=DEV,
+                                        head_weights=q, **kw)
+    want, best = oracle.forward(x, th, layers, c, binary_bits=b if binary else 0)
+    if dsp:
+        want, best = oracle.grouped_dsp(want, q)
+    xd = torch.from_numpy(x).to(DEV)
+    for switch in (None, "0"):
+        if switch is None:
+            monkeypatch.delenv("BITLOGIC_JUMP_LAYER", raising=False)
+        else:
+            monkeypatch.setenv("BITLOGIC_JUMP_LAYER", switch)
+        ws = torch.full((model.workspace_bytes(n),), 0xA5, dtype=torch.uint8, device=DEV)
+        out, am = model.forward(xd, workspace=ws)
+        none, only = model.forward(xd, workspace=ws, want_scores=False)
+        assert none is None
+        assert np.array_equal(out.cpu().numpy(), want), switch
+        assert np.array_equal(am.cpu().numpy(), best), switch
+        assert np.array_equal(only.cpu().numpy(), best), switch
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000])
+@pytest.mark.parametrize("b", range(1, 9))
+def test_encoder_widths_and_batches(monkeypatch, n, b):
+    check(monkeypatch, n, 97 + b, b, (300, 130), 1 + b % 6, 10, dsp=b % 2 == 0, binary=b % 3 == 0)
+    check(monkeypatch, n, 3, b, (70, 66), min(3, 1 + b % 6), 11, binary=b % 3 == 1)
+
+
+@pytest.mark.parametrize("k", range(1, 7))
+def test_fan_ins(monkeypatch, k):
+    check(monkeypatch, 200, 60, 4, (257, 511, 640), k, 10)
+    check(monkeypatch, 129, 60, 4, (300, 260), (k, 7 - k), 13, dsp=True)
+
+
+@pytest.mark.parametrize("n,widths,k,c", [
+    (130, (500, 7), 4, 7),              # one node a class: 64 classes in a wave's word
+    (130, (500, 300), 4, 300),          # more classes than waves
+    (65, (200, 3990), 3, 10),           # one block, 399 nodes a class
+    (65, (200, 12000), 3, 10),          # classes over several blocks
+    (65, (200, 10000), 3, 2),           # a class longer than a block's rounds
+    (65, (21001, 900), 3, 10),          # input rows past the LDS: gathered
+    (70, (19999, 900), 2, 10),          # input rows that just fit
+    (64 * 40, (9001, 100), 2, 10),      # two columns a lane
+    (64 * 60 - 1, (9001, 100), 2, 10),  # four columns a lane, a ragged group
+    (64 * 61, (9001, 100), 4, 10),
+])
+def test_shapes(monkeypatch, n, widths, k, c):
+    check(monkeypatch, n, 40, 3, widths, k, c)
+    if c <= 128:
+        check(monkeypatch, n, 40, 3, widths, k, c, dsp=True, seed=1)
+
+
+def test_stage_events():
+    rng = np.random.default_rng(5)
+    layers, w_in = [], 80
+    for w in (100, 90):
+        layers.append((draw_connectivity(rng, w, 4, w_in),
+                       rng.integers(0, 1 << 16, size=w, dtype=np.uint64)))
+        w_in = w
+    th = rng.integers(0, 256, size=(40, 2), dtype=np.uint8)
+    x = rng.integers(0, 256, size=(100, 40), dtype=np.uint8)
+    model = bl.BitlogicModel.from_numpy(th, layers, 10, device=DEV)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
+    for e in ev:
+        e.record()
+    out, _ = model.forward(torch.from_numpy(x).to(DEV), events=ev)
+    torch.cuda.synchronize()
+    assert all(ev[i].elapsed_time(ev[i + 1]) >= 0 for i in range(4))
+    assert np.array_equal(out.cpu().numpy(), oracle.forward(x, th, layers, 10)[0])
