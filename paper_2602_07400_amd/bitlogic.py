@@ -142,8 +142,14 @@ def words(n_samples: int) -> int:
     return (int(n_samples) + 63) // 64
 
 
+# the current stream's handle without building a torch.cuda.Stream around it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream, device) -> int:
     if stream is None:
+        if _raw_stream is not None and device.index is not None:
+            return _raw_stream(device.index)
         return torch.cuda.current_stream(device).cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
@@ -151,15 +157,15 @@ def _stream(stream, device) -> int:
 
 
 def _dev(t: torch.Tensor, name: str, dtypes) -> int:
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype in dtypes and t.is_contiguous():
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if not t.is_cuda:
         raise ValueError(f"{name} must be on the GPU")
     if t.dtype not in dtypes:
         raise TypeError(f"{name} has dtype {t.dtype}, expected one of {dtypes}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return t.data_ptr()
+    raise ValueError(f"{name} must be contiguous")
 
 
 _U8 = (torch.uint8,)
@@ -209,19 +215,21 @@ def _on_stream(t: Optional[torch.Tensor], handle: int, device) -> Optional[torch
 
 def _empty(shape, dtype, device, stream) -> torch.Tensor:
     """An output this module allocates for a call on `stream` (see _on_stream)."""
+    if stream is None:
+        return torch.empty(shape, dtype=dtype, device=device)
     return _on_stream(torch.empty(shape, dtype=dtype, device=device), _stream(stream, device),
                       device)
 
 
 def _workspace(nbytes: int, device, given: Optional[torch.Tensor],
-               handle: Optional[int] = None) -> Tuple[int, int]:
+               stream=None) -> Tuple[int, int]:
     if given is not None:
         return _dev(given, "workspace", (torch.uint8,)), given.numel()
     if nbytes == 0:
         return 0, 0
     buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
-    if handle is not None:
-        _on_stream(buf, handle, device)
+    if stream is not None:
+        _on_stream(buf, _stream(stream, device), device)
     _workspace.keep = buf        # kept alive until the next call allocates one
     return buf.data_ptr(), nbytes
 
@@ -239,7 +247,7 @@ def bitlogic_groupsum_head(bits: torch.Tensor, n_samples: int, n_classes: int,
     if argmax is None:
         argmax = _empty((n_samples,), torch.int32, dev, stream)
     ws_ptr, ws_bytes = _workspace(bitlogic_groupsum_head_workspace_bytes(w, n_samples, n_classes),
-                                  dev, workspace, _stream(stream, dev))
+                                  dev, workspace, stream)
     _check(load_library().bitlogic_groupsum_head(
         _dev(bits, "bits", _U64), w, n_samples, n_classes,
         _dev(scores, "scores", _I32) if scores is not None else None,
@@ -248,20 +256,19 @@ def bitlogic_groupsum_head(bits: torch.Tensor, n_samples: int, n_classes: int,
 
 
 def _layer_array(layers: Sequence[Tuple[torch.Tensor, torch.Tensor]]):
-    arr = (_Layer * len(layers))()
+    descr = []
     for l, (conn, tables) in enumerate(layers):
-        arr[l].conn = _dev(conn, f"conn[{l}]", _I32)
-        arr[l].tables = _dev(tables, f"tables[{l}]", _U64)
-        arr[l].w_out = conn.shape[0]
-        arr[l].k = conn.shape[1]
-    return arr
+        shape = conn.shape
+        descr.append(_Layer(_dev(conn, f"conn[{l}]", _I32), _dev(tables, f"tables[{l}]", _U64),
+                            shape[0], shape[1]))
+    return (_Layer * len(descr))(*descr)
 
 
 def bitlogic_forward_workspace_bytes(n_samples: int, n_features: int, n_thresholds: int,
                                      layers, n_classes: int) -> int:
     arr = _layer_array(layers)
     return int(load_library().bitlogic_forward_workspace_bytes(
-        n_samples, n_features, n_thresholds, ctypes.cast(arr, ctypes.c_void_p), len(layers),
+        n_samples, n_features, n_thresholds, ctypes.addressof(arr), len(layers),
         n_classes))
 
 
@@ -272,7 +279,7 @@ def bitlogic_forward_plan(n_samples: int, n_features: int, n_thresholds: int,
     arr = _layer_array(layers)
     info = _ForwardInfo()
     _check(load_library().bitlogic_forward_plan(
-        n_samples, n_features, n_thresholds, ctypes.cast(arr, ctypes.c_void_p), len(layers),
+        n_samples, n_features, n_thresholds, ctypes.addressof(arr), len(layers),
         n_classes, ctypes.byref(info)))
     return {"workspace_bytes": int(info.workspace_bytes), "slab_words": int(info.slab_words),
             "fused_head": bool(info.fused_head), "head_splits": int(info.head_splits),
@@ -307,7 +314,7 @@ def bitlogic_fit_quantile_thresholds(x: torch.Tensor, n_thresholds: int, n_group
         out = _empty((d, n_thresholds), torch.uint8, dev, stream)
     lib = load_library()
     need = int(lib.bitlogic_fit_quantile_thresholds_workspace_bytes(int(n_groups)))
-    ws_ptr, ws_bytes = _workspace(max(need, 8), dev, workspace, _stream(stream, dev))
+    ws_ptr, ws_bytes = _workspace(max(need, 8), dev, workspace, stream)
     _check(lib.bitlogic_fit_quantile_thresholds(_dev(x, "x", _U8), n, d, int(n_thresholds),
                                                 int(n_groups), _dev(out, "out", _U8), ws_ptr,
                                                 ws_bytes, _stream(stream, dev)))
@@ -350,15 +357,15 @@ def bitlogic_forward_grouped_dsp(x: torch.Tensor, thresholds: torch.Tensor,
     arr = _layer_array(layers)
     lib = load_library()
     need = int(lib.bitlogic_forward_workspace_bytes(
-        n, d, b, ctypes.cast(arr, ctypes.c_void_p), len(arr), n_classes))
+        n, d, b, ctypes.addressof(arr), len(arr), n_classes))
     if logits is None and want_logits:
         logits = _empty((n, n_classes), torch.int32, dev, stream)
     if argmax is None:
         argmax = _empty((n,), torch.int32, dev, stream)
-    ws_ptr, ws_bytes = _workspace(need, dev, workspace, _stream(stream, dev))
+    ws_ptr, ws_bytes = _workspace(need, dev, workspace, stream)
     _check(lib.bitlogic_forward_grouped_dsp(
         _dev(x, "x", _U8), n, d, _dev(thresholds, "thresholds", _U8), b,
-        ctypes.cast(arr, ctypes.c_void_p), len(arr), n_classes, _dev(weights, "weights", _I8),
+        ctypes.addressof(arr), len(arr), n_classes, _dev(weights, "weights", _I8),
         _dev(logits, "logits", _I32) if logits is not None else None,
         _dev(argmax, "argmax", _I32), ws_ptr, ws_bytes, _stream(stream, dev)))
     return logits, argmax
@@ -372,14 +379,14 @@ def _forward(x, thresholds, layers, n_classes, scores, argmax, workspace, stream
     arr = _layer_array(layers)
     lib = load_library()
     need = int(lib.bitlogic_forward_workspace_bytes(
-        n, d, b, ctypes.cast(arr, ctypes.c_void_p), len(arr), n_classes))
+        n, d, b, ctypes.addressof(arr), len(arr), n_classes))
     if scores is None and want_scores:
         scores = _empty((n, n_classes), torch.int32, dev, stream)
     if argmax is None:
         argmax = _empty((n,), torch.int32, dev, stream)
-    ws_ptr, ws_bytes = _workspace(need, dev, workspace, _stream(stream, dev))
+    ws_ptr, ws_bytes = _workspace(need, dev, workspace, stream)
     args = [_dev(x, "x", _U8), n, d, _dev(thresholds, "thresholds", _U8), b,
-            ctypes.cast(arr, ctypes.c_void_p), len(arr), n_classes,
+            ctypes.addressof(arr), len(arr), n_classes,
             _dev(scores, "scores", _I32) if scores is not None else None,
             _dev(argmax, "argmax", _I32), ws_ptr, ws_bytes, _stream(stream, dev)]
     if events is None:
@@ -561,21 +568,17 @@ class BitlogicModel:
         ptrs = (ctypes.c_void_p * len(self.layers))(
             *[None if f is None else _dev(f, "pass_fanin", (torch.uint8,))
               for f in self.pass_fanin])
-        return ctypes.cast(ptrs, ctypes.c_void_p), ptrs
+        return ctypes.addressof(ptrs), ptrs
 
     def _net(self):
         arr = _layer_array(self.layers)
-        net = _Network()
-        net.n_features, net.encoder, net.n_bits = self.n_features, self.encoder, self.n_bits
-        net.thresholds = (_dev(self.thresholds, "thresholds", _U8)
-                          if self.thresholds is not None else None)
-        net.layers = ctypes.cast(arr, ctypes.c_void_p)
-        net.n_layers = len(self.layers)
-        net.n_classes = self.n_classes
-        net.head = self.head
-        net.head_weights = (_dev(self.head_weights, "head_weights", _I8)
-                            if self.head_weights is not None else None)
-        net.pass_fanin, keep = self._fanin_array()
+        fanin, keep = self._fanin_array()
+        net = _Network(
+            self.n_features, self.encoder, self.n_bits,
+            _dev(self.thresholds, "thresholds", _U8) if self.thresholds is not None else None,
+            ctypes.addressof(arr), len(arr), self.n_classes, self.head,
+            _dev(self.head_weights, "head_weights", _I8) if self.head_weights is not None
+            else None, fanin)
         return net, (arr, keep)
 
     def workspace_bytes(self, n_samples: int) -> int:
@@ -619,7 +622,7 @@ def bitlogic_network_forward(model: BitlogicModel, x: torch.Tensor,
         out = _empty((n, model.n_classes), torch.int32, dev, stream)
     if argmax is None:
         argmax = _empty((n,), torch.int32, dev, stream)
-    ws_ptr, ws_bytes = _workspace(need, dev, workspace, _stream(stream, dev))
+    ws_ptr, ws_bytes = _workspace(need, dev, workspace, stream)
     if events is None:
         ev_ptr, n_ev = None, 0
     else:
