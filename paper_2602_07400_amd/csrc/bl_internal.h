@@ -23,6 +23,8 @@ constexpr int kSlabLanes = BL_SLAB_LPN;
 static_assert(kSlabWords % kSlabLanes == 0, "each lane takes whole words");
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// four dwords at an 8-byte aligned address (one load or store all the same)
+typedef u32x4 u32x4_a8 __attribute__((aligned(8)));
 
 // Layouts of packed bit tensors: row-major [rows][W] (the public calls) or
 // slabs (bitlogic_forward's intermediates in its workspace).

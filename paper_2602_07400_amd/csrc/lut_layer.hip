@@ -31,122 +31,8 @@ namespace bl {
 namespace {
 
 using dev::eval_node;
-using dev::mux_tree;
 
 constexpr int kThreads = 256;
-constexpr int kWavesPerBlock = kThreads / kWave;
-
-// Access modes: whole windows with 16-byte or 8-byte accesses, or the one
-// ragged last window with per-word guards.  Separate instantiations keep the
-// guards out of the hot loop.
-enum Mode { kFull16 = 0, kFull8 = 1, kTail = 2 };
-
-template <int K, int LPN, int R, int NB, int MODE>
-__global__ __launch_bounds__(kThreads) void k_lut_layer(
-    const uint64_t *__restrict__ in, int64_t W, const int32_t *__restrict__ conn,
-    const uint64_t *__restrict__ tables, int32_t w_out, uint64_t *__restrict__ out,
-    int32_t n_nblk, int32_t n_win, int32_t win_base)
-{
-    constexpr int kGroups = kWave / LPN;                  // nodes per wave per pass
-    constexpr int kPassNodes = kGroups * kWavesPerBlock;  // nodes per block per pass
-    constexpr int kWin = LPN * R;                         // words per window
-    static_assert(NB % kPassNodes == 0, "node block must be whole passes");
-    static_assert(MODE != kFull16 || R % 2 == 0, "16-byte path needs an even R");
-
-    __shared__ int32_t s_conn[NB * K];
-    __shared__ uint64_t s_tab[NB];
-
-    int win, nblk;
-    if (!dealt_task(blockIdx.x, n_win - win_base, n_nblk, win, nblk))
-        return;
-    win += win_base;
-    const int node0 = nblk * NB;
-    const int nodes = min(NB, w_out - node0);
-
-    for (int q = threadIdx.x; q < NB * K; q += kThreads)
-        s_conn[q] = (q < nodes * K) ? conn[(int64_t)node0 * K + q] : 0;
-    for (int q = threadIdx.x; q < NB; q += kThreads)
-        s_tab[q] = (q < nodes) ? tables[node0 + q] : 0;
-    __syncthreads();
-
-    const int lane = threadIdx.x % kWave;
-    const int wave = threadIdx.x / kWave;
-    const int grp = lane / LPN;
-    const int sub = lane % LPN;
-    const int64_t wb0 = (int64_t)win * kWin + (int64_t)sub * R;
-
-#pragma unroll 1
-    for (int pass = 0; pass < NB / kPassNodes; ++pass) {
-        if (pass * kPassNodes >= nodes)
-            break;
-        const int jl = pass * kPassNodes + wave * kGroups + grp;
-
-        // gather the K input words of each of this lane's R words
-        uint32_t xv[2 * R][K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-            const uint64_t *src = in + (int64_t)s_conn[jl * K + i] * W + wb0;
-            if constexpr (MODE == kFull16) {
-#pragma unroll
-                for (int r = 0; r < R; r += 2) {
-                    const uint4 v = reinterpret_cast<const uint4 *>(src)[r / 2];
-                    xv[2 * r + 0][i] = v.x;
-                    xv[2 * r + 1][i] = v.y;
-                    xv[2 * r + 2][i] = v.z;
-                    xv[2 * r + 3][i] = v.w;
-                }
-            } else if constexpr (MODE == kFull8) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const uint2 v = reinterpret_cast<const uint2 *>(src)[r];
-                    xv[2 * r + 0][i] = v.x;
-                    xv[2 * r + 1][i] = v.y;
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    // words past the end read the row's last word (discarded)
-                    const int64_t idx = min(wb0 + r, W - 1) - wb0;
-                    const uint2 v = reinterpret_cast<const uint2 *>(src)[idx];
-                    xv[2 * r + 0][i] = v.x;
-                    xv[2 * r + 1][i] = v.y;
-                }
-            }
-        }
-
-        // table entries -> full-word masks (one v_bfe_i32 each)
-        const uint64_t T = s_tab[jl];
-        const uint32_t t_lo = (uint32_t)T, t_hi = (uint32_t)(T >> 32);
-        uint32_t m[1 << K];
-#pragma unroll
-        for (int a = 0; a < (1 << K); ++a)
-            m[a] = 0u - (((a < 32 ? t_lo : t_hi) >> (a & 31)) & 1u);
-
-        uint32_t o[2 * R];
-#pragma unroll
-        for (int h = 0; h < 2 * R; ++h)
-            o[h] = mux_tree<K>(xv[h], m);
-
-        if (jl < nodes) {
-            uint64_t *dst = out + (int64_t)(node0 + jl) * W + wb0;
-            if constexpr (MODE == kFull16) {
-#pragma unroll
-                for (int r = 0; r < R; r += 2)
-                    reinterpret_cast<uint4 *>(dst)[r / 2] =
-                        make_uint4(o[2 * r], o[2 * r + 1], o[2 * r + 2], o[2 * r + 3]);
-            } else if constexpr (MODE == kFull8) {
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                    reinterpret_cast<uint2 *>(dst)[r] = make_uint2(o[2 * r], o[2 * r + 1]);
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (wb0 + r < W)
-                        reinterpret_cast<uint2 *>(dst)[r] = make_uint2(o[2 * r], o[2 * r + 1]);
-            }
-        }
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Slab layout (used for the intermediate tensors of bitlogic_forward): the
@@ -163,7 +49,7 @@ __global__ __launch_bounds__(kThreads) void k_lut_layer(
 #endif
 
 template <int K, int R>
-__device__ __forceinline__ void gather(const uint64_t *src, const int32_t *c, int S,
+__device__ __forceinline__ void gather(const uint64_t *src, const int32_t *c, int64_t S,
                                        uint32_t (&xv)[2 * R][K])
 {
 #pragma unroll
@@ -176,7 +62,7 @@ __device__ __forceinline__ void gather(const uint64_t *src, const int32_t *c, in
         } else {
 #pragma unroll
             for (int r = 0; r < R; r += 2) {
-                const u32x4 a = reinterpret_cast<const u32x4 *>(p)[r / 2];
+                const u32x4 a = reinterpret_cast<const u32x4_a8 *>(p)[r / 2];
                 xv[2 * r + 0][i] = a.x;
                 xv[2 * r + 1][i] = a.y;
                 xv[2 * r + 2][i] = a.z;
@@ -232,9 +118,9 @@ __device__ __forceinline__ void store_out(const uint32_t (&o)[2 * R], uint64_t *
             for (int r = 0; r < R; r += 2) {
                 const u32x4 v = u32x4{o[2 * r], o[2 * r + 1], o[2 * r + 2], o[2 * r + 3]};
                 if (BL_NT_STORE)
-                    __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(q) + r / 2);
+                    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_a8 *>(q) + r / 2);
                 else
-                    reinterpret_cast<u32x4 *>(q)[r / 2] = v;
+                    reinterpret_cast<u32x4_a8 *>(q)[r / 2] = v;
             }
         }
     }
@@ -257,7 +143,7 @@ __device__ __forceinline__ void eval_store(uint64_t T, const uint32_t (&xv)[2 * 
 // pass gathers kp wires and runs the 2^kp - 1 multiplexer tree; kp = 0 is a
 // constant node (table bit 0).
 template <int KQ, int K, int R>
-__device__ __forceinline__ void spec_eval(int kp, const uint64_t *src, const int32_t *c, int S,
+__device__ __forceinline__ void spec_eval(int kp, const uint64_t *src, const int32_t *c, int64_t S,
                                           uint64_t T, uint32_t (&o)[2 * R])
 {
     if constexpr (KQ == 0) {
@@ -377,7 +263,7 @@ constexpr int split_depth()
 // (table bit 0).
 template <int KP, int KS, int R, int NPASS, int kPassNodes>
 __device__ __forceinline__ void split_passes(const uint64_t *src, const int32_t *s_conn,
-                                             const uint64_t *s_tab, int lnode, int S,
+                                             const uint64_t *s_tab, int lnode, int64_t S,
                                              uint64_t *dst)
 {
     uint32_t o[NPASS][2 * R];
@@ -421,7 +307,7 @@ __device__ __forceinline__ void split_passes(const uint64_t *src, const int32_t 
 template <int KQ, int K, int R, int NPASS, int kPassNodes>
 __device__ __forceinline__ void split_passes_kp(int kp, const uint64_t *src,
                                                 const int32_t *s_conn, const uint64_t *s_tab,
-                                                int lnode, int S, uint64_t *dst)
+                                                int lnode, int64_t S, uint64_t *dst)
 {
     if (kp == KQ) {
         split_passes<KQ, K, R, NPASS, kPassNodes>(src, s_conn, s_tab, lnode, S, dst);
@@ -957,44 +843,117 @@ hipError_t launch_slab_head_k(const uint64_t *in, int32_t w_in, int64_t n_slabs,
     }
 }
 
-constexpr int kLPN = 4;
-constexpr int kR = 4;
-constexpr int kNB = 256;
+// ---------------------------------------------------------------------------
+// Row-major tensors (bitlogic_lut_layer): rows of W words, cut into windows of
+// kSlabWords words that take the place of the slabs.  The lines of a window lie
+// a row apart, so where a row is a large power of two they crowd into few sets
+// of the caches (32000 rows of 1024 words: 285 us, of 1040 words: 212).  Eight
+// lanes share a node at every fan-in: one load instruction then takes a whole
+// line, where two loads of half its pieces each found it evicted in between
+// (fan-in 5, 8000 -> 8000, W = 4096: four lanes 272 us, eight 193; fan-in 6,
+// 32000 -> 32000, W = 1024: 287, 235; rows that do not crowd, 9216 -> 32000 at
+// fan-in 6, W = 1040: 156, 169).  Loads and stores are 16 bytes at any 8-byte
+// address, so rows of an odd word count take no other path; stores are
+// non-temporal, as in the slab kernel; a ragged last window is part of the same
+// launch.  Against the kernel before (four lanes, plain stores, 8-byte accesses
+// for odd rows, the tail a launch of its own, 256-node blocks): 9216 -> 32000 at
+// fan-in 4, W = 1024 195 -> 101 us, 3920 -> 8011 at fan-in 4, W = 313 28.5 ->
+// 13.4, 9216 -> 32000 at fan-in 6, W = 1023 262 -> 206.
+constexpr int kRowsLPN = 8;
+// Nodes per block: 128 (4 passes) where that gives enough blocks, else one pass.
+// 256 and 512 were slower where lines crowd (8000 -> 8000 at fan-in 5, W = 4100:
+// 159, 233 and 302 us) and equal elsewhere; one pass is faster below the bound
+// (30000 -> 20000 at fan-in 5, W = 300, 2983 blocks of 128: 53.5 against 45.6).
+constexpr int kRowsNB = 128;
+constexpr int64_t kRowsSmallBlocks = 4096;
 
-template <int K, int MODE>
-hipError_t launch_mode(const uint64_t *in, int64_t W, const int32_t *conn,
-                       const uint64_t *tables, int32_t w_out, uint64_t *out,
-                       int64_t win_base, int64_t n_win, hipStream_t stream)
+template <int K, int LPN, int NB>
+__global__ __launch_bounds__(kThreads) void k_lut_rows(
+    const uint64_t *__restrict__ in, int64_t W, const int32_t *__restrict__ conn,
+    const uint64_t *__restrict__ tables, int32_t w_out, uint64_t *__restrict__ out,
+    int32_t n_nblk, int32_t n_win)
 {
-    const int32_t n_nblk = (w_out + kNB - 1) / kNB;
-    const int64_t blocks = dealt_blocks(n_win - win_base, n_nblk);
+    constexpr int R = kSlabWords / LPN;                // words per lane
+    constexpr int kPassNodes = kThreads / LPN;
+    constexpr int kPasses = NB / kPassNodes;
+    static_assert(NB % kPassNodes == 0, "node block must be whole passes");
+    __shared__ int32_t s_conn[NB * K];
+    __shared__ uint64_t s_tab[NB];
+
+    int win, nblk;
+    if (!dealt_task(blockIdx.x, n_win, n_nblk, win, nblk))
+        return;
+    const int node0 = nblk * NB;
+    const int nodes = min(NB, w_out - node0);
+    for (int q = threadIdx.x; q < NB * K; q += kThreads)
+        s_conn[q] = (q < nodes * K) ? conn[(int64_t)node0 * K + q] : 0;
+    for (int q = threadIdx.x; q < NB; q += kThreads)
+        s_tab[q] = (q < nodes) ? tables[node0 + q] : 0;
+    __syncthreads();
+
+    const int sub = threadIdx.x % LPN;
+    const int lnode = threadIdx.x / LPN;
+    const int64_t wb0 = (int64_t)win * kSlabWords + sub * R;
+    const uint64_t *src = in + wb0;
+    uint64_t *dst = out + (int64_t)node0 * W + wb0;
+    const int npass = (nodes + kPassNodes - 1) / kPassNodes;
+    if ((int64_t)(win + 1) * kSlabWords <= W) {
+        if constexpr (slab_prefetch<K>() && kPasses >= 2) {
+            if (nodes == NB) {
+                split_passes<K, K, R, kPasses, kPassNodes>(src, s_conn, s_tab, lnode, W, dst);
+                return;
+            }
+        }
+#pragma unroll 1
+        for (int pass = 0; pass < npass; ++pass) {
+            const int jl = pass * kPassNodes + lnode;
+            uint32_t xv[2 * R][K];
+            gather<K, R>(src, &s_conn[jl * K], W, xv);
+            eval_store<K, R>(s_tab[jl], xv, dst + jl * W, jl < nodes);
+        }
+        return;
+    }
+    // the ragged last window, a word at a time: words past the end read the
+    // row's last word and are not stored
+#pragma unroll 1
+    for (int pass = 0; pass < npass; ++pass) {
+        const int jl = pass * kPassNodes + lnode;
+#pragma unroll 1
+        for (int r = 0; r < R; ++r) {
+            uint32_t xv[2][K], o[2];
+            gather<K, 1>(in + min(wb0 + r, W - 1), &s_conn[jl * K], W, xv);
+            eval_node<K, 1>(s_tab[jl], xv, o);
+            store_out<1>(o, dst + jl * W + r, jl < nodes && wb0 + r < W);
+        }
+    }
+}
+
+template <int K, int NB>
+hipError_t launch_rows_kn(const uint64_t *in, int64_t W, const int32_t *conn,
+                          const uint64_t *tables, int32_t w_out, uint64_t *out,
+                          hipStream_t stream)
+{
+    const int64_t n_win = (W + kSlabWords - 1) / kSlabWords;
+    const int32_t n_nblk = (w_out + NB - 1) / NB;
+    const int64_t blocks = dealt_blocks(n_win, n_nblk);
     if (blocks > 0x7fffffff || n_win > 0x7fffffff)
         return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((k_lut_layer<K, kLPN, kR, kNB, MODE>), dim3((unsigned)blocks),
+    hipLaunchKernelGGL((k_lut_rows<K, kRowsLPN, NB>), dim3((unsigned)blocks),
                        dim3(kThreads), 0, stream, in, W, conn, tables, w_out, out, n_nblk,
-                       (int32_t)n_win, (int32_t)win_base);
+                       (int32_t)n_win);
     return hipGetLastError();
 }
 
 template <int K>
-hipError_t launch_k(const uint64_t *in, int64_t W, const int32_t *conn,
-                    const uint64_t *tables, int32_t w_out, uint64_t *out,
-                    hipStream_t stream)
+hipError_t launch_rows_k(const uint64_t *in, int64_t W, const int32_t *conn,
+                         const uint64_t *tables, int32_t w_out, uint64_t *out,
+                         hipStream_t stream)
 {
-    constexpr int kWin = kLPN * kR;
-    const int64_t n_full = W / kWin;
-    hipError_t e = hipSuccess;
-    if (n_full > 0) {
-        const bool vec16 = (W % 2 == 0) && ((uintptr_t)in % 16 == 0) &&
-                           ((uintptr_t)out % 16 == 0);
-        e = vec16 ? launch_mode<K, kFull16>(in, W, conn, tables, w_out, out, 0, n_full, stream)
-                  : launch_mode<K, kFull8>(in, W, conn, tables, w_out, out, 0, n_full, stream);
-        if (e != hipSuccess)
-            return e;
-    }
-    if (W % kWin != 0)
-        e = launch_mode<K, kTail>(in, W, conn, tables, w_out, out, n_full, n_full + 1, stream);
-    return e;
+    const int64_t n_win = (W + kSlabWords - 1) / kSlabWords;
+    if (n_win * ((w_out + kRowsNB - 1) / kRowsNB) < kRowsSmallBlocks)
+        return launch_rows_kn<K, kThreads / kRowsLPN>(in, W, conn, tables, w_out, out,
+                                                             stream);
+    return launch_rows_kn<K, kRowsNB>(in, W, conn, tables, w_out, out, stream);
 }
 
 }  // namespace
@@ -1063,12 +1022,12 @@ hipError_t launch_lut_layer(const uint64_t *in, int32_t w_in, int64_t n_words,
 {
     (void)w_in;
     switch (k) {
-    case 1: return launch_k<1>(in, n_words, conn, tables, w_out, out, stream);
-    case 2: return launch_k<2>(in, n_words, conn, tables, w_out, out, stream);
-    case 3: return launch_k<3>(in, n_words, conn, tables, w_out, out, stream);
-    case 4: return launch_k<4>(in, n_words, conn, tables, w_out, out, stream);
-    case 5: return launch_k<5>(in, n_words, conn, tables, w_out, out, stream);
-    case 6: return launch_k<6>(in, n_words, conn, tables, w_out, out, stream);
+    case 1: return launch_rows_k<1>(in, n_words, conn, tables, w_out, out, stream);
+    case 2: return launch_rows_k<2>(in, n_words, conn, tables, w_out, out, stream);
+    case 3: return launch_rows_k<3>(in, n_words, conn, tables, w_out, out, stream);
+    case 4: return launch_rows_k<4>(in, n_words, conn, tables, w_out, out, stream);
+    case 5: return launch_rows_k<5>(in, n_words, conn, tables, w_out, out, stream);
+    case 6: return launch_rows_k<6>(in, n_words, conn, tables, w_out, out, stream);
     default: return hipErrorInvalidValue;
     }
 }
