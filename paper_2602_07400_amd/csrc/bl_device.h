@@ -1,6 +1,6 @@
 // Device helpers shared by the kernels of libbitlogic (internal).
 //
-//  * bfi_asm, swap_stage, transpose64: the 64x64 bit transpose across a wave
+//  * swap_stage, transpose64: the 64x64 bit transpose across a wave
 //    that turns per-sample rows of wire bits into per-wire words of 64
 //    samples (the encoders);
 //  * mux_tree, subtree, eval_node: a LUT node on bit-sliced words, its 2^K
@@ -27,57 +27,6 @@ extern "C" __device__ int bl_writelane(int value, int lane, int old)
 namespace bl {
 namespace dev {
 
-// (sel & one) | (~sel & zero) as a single v_bfi_b32 (left to itself the
-// compiler splits it into and/or with an extra inverted-mask register)
-__device__ __forceinline__ uint32_t bfi_asm(uint32_t sel, uint32_t one, uint32_t zero)
-{
-    uint32_t r;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(sel), "v"(one), "v"(zero));
-    return r;
-}
-
-// One block-swap stage of the 32x32 transpose inside each 32-lane half: lanes
-// l and l^S exchange the S-bit blocks that sit off the diagonal.
-template <int S, int K>
-__device__ __forceinline__ void swap_stage(uint32_t &v, const uint32_t (&amt)[5],
-                                           const uint32_t (&msk)[5])
-{
-    constexpr int kPattern = 0x1F | (S << 10);     // ds_swizzle bit mode: lane ^ S
-    const uint32_t y = (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, kPattern);
-    v = bfi_asm(msk[K], v, __builtin_amdgcn_alignbit(y, y, amt[K]));
-}
-
-// 64x64 bit transpose across a wave.  In: lane l holds bits (lo, hi) = row l.
-// Out: lane p holds column p (bit l of (lo, hi) = old bit p of lane l).
-__device__ __forceinline__ void transpose64(uint32_t &lo, uint32_t &hi,
-                                            const uint32_t (&amt)[5], const uint32_t (&msk)[5])
-{
-    // off-diagonal 32x32 blocks: hi of lanes 0..31 <-> lo of lanes 32..63
-    const auto sw = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
-    lo = sw[0];
-    hi = sw[1];
-    // each register is now a 32x32 block per 32-lane half: recursive block swap
-    swap_stage<16, 0>(lo, amt, msk); swap_stage<16, 0>(hi, amt, msk);
-    swap_stage<8, 1>(lo, amt, msk);  swap_stage<8, 1>(hi, amt, msk);
-    swap_stage<4, 2>(lo, amt, msk);  swap_stage<4, 2>(hi, amt, msk);
-    swap_stage<2, 3>(lo, amt, msk);  swap_stage<2, 3>(hi, amt, msk);
-    swap_stage<1, 4>(lo, amt, msk);  swap_stage<1, 4>(hi, amt, msk);
-}
-
-// Per-lane constants of transpose64: rotate amounts and merge masks of its
-// five block-swap stages.
-__device__ __forceinline__ void transpose_consts(int lane, uint32_t (&amt)[5], uint32_t (&msk)[5])
-{
-    const uint32_t low[5] = {0x0000FFFFu, 0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const int s = 16 >> k;
-        const bool up = (lane & s) != 0;
-        amt[k] = up ? s : 32 - s;
-        msk[k] = up ? ~low[k] : low[k];
-    }
-}
-
 // The bitwise multiplexer (sel & one) | (~sel & zero).  As v_bitop3_b32 with
 // truth table 0xCA (bit (sel << 2 | one << 1 | zero) of the table is the
 // result): chains of it sustain about 59 T lane-ops/s on gfx950 (75% of the
@@ -90,6 +39,62 @@ __device__ __forceinline__ uint32_t bfi(uint32_t sel, uint32_t one, uint32_t zer
 #else
     return (sel & one) | (~sel & zero);
 #endif
+}
+
+// Per-lane constants of transpose64: byte selectors of its first two block
+// swaps, rotate amounts and merge masks of the other three.
+struct Transpose {
+    uint32_t sel[2], amt[3], msk[3];
+};
+
+__device__ __forceinline__ Transpose transpose_consts(int lane)
+{
+    const uint32_t low[3] = {0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
+    Transpose c;
+    c.sel[0] = (lane & 16) ? 0x07060302u : 0x01000504u;
+    c.sel[1] = (lane & 8) ? 0x07030501u : 0x02060004u;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int s = 4 >> k;
+        const bool up = (lane & s) != 0;
+        c.amt[k] = up ? s : 32 - s;
+        c.msk[k] = up ? ~low[k] : low[k];
+    }
+    return c;
+}
+
+// One block-swap stage of the 32x32 transpose inside each 32-lane half: lanes
+// l and l^S exchange the S-bit blocks that sit off the diagonal.  Blocks of 16
+// and 8 bits are whole bytes, one v_perm; the others rotate the partner's word
+// and merge it, the merge as v_bitop3 on VGPRs, which issues at the full rate
+// (55 T lane-ops/s; v_bfi, v_alignbit and v_perm 35).
+template <int S>
+__device__ __forceinline__ void swap_stage(uint32_t &v, const Transpose &c)
+{
+    constexpr int kPattern = 0x1F | (S << 10);     // ds_swizzle bit mode: lane ^ S
+    const uint32_t y = (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, kPattern);
+    if constexpr (S >= 8) {
+        v = __builtin_amdgcn_perm(v, y, c.sel[S == 8]);
+    } else {
+        constexpr int k = S == 4 ? 0 : S == 2 ? 1 : 2;
+        v = bfi(c.msk[k], v, __builtin_amdgcn_alignbit(y, y, c.amt[k]));
+    }
+}
+
+// 64x64 bit transpose across a wave.  In: lane l holds bits (lo, hi) = row l.
+// Out: lane p holds column p (bit l of (lo, hi) = old bit p of lane l).
+__device__ __forceinline__ void transpose64(uint32_t &lo, uint32_t &hi, const Transpose &c)
+{
+    // off-diagonal 32x32 blocks: hi of lanes 0..31 <-> lo of lanes 32..63
+    const auto sw = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+    lo = sw[0];
+    hi = sw[1];
+    // each register is now a 32x32 block per 32-lane half: recursive block swap
+    swap_stage<16>(lo, c); swap_stage<16>(hi, c);
+    swap_stage<8>(lo, c);  swap_stage<8>(hi, c);
+    swap_stage<4>(lo, c);  swap_stage<4>(hi, c);
+    swap_stage<2>(lo, c);  swap_stage<2>(hi, c);
+    swap_stage<1>(lo, c);  swap_stage<1>(hi, c);
 }
 
 // Fold 2^K masks with K select words: level i pairs entries that differ in

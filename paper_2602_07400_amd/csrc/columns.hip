@@ -203,8 +203,7 @@ __global__ __launch_bounds__(kHeadThreads) void k_col_head(
         s_cnt[e] = 0;
     __syncthreads();
 
-    uint32_t amt[5], msk[5];
-    transpose_consts(lane, amt, msk);
+    const dev::Transpose tr = transpose_consts(lane);
     while (base < n1) {
         uint32_t xv[2][K], o[2];
 #pragma unroll
@@ -219,7 +218,7 @@ __global__ __launch_bounds__(kHeadThreads) void k_col_head(
             fetch(next);
         eval_node<K, 1>(Tc, xv, o);
         // lane = node -> lane = sample, bit l = node base + l
-        transpose64(o[0], o[1], amt, msk);
+        transpose64(o[0], o[1], tr);
         const uint64_t bits = (uint64_t)o[1] << 32 | o[0];
         const int end = min(base + kWave, n1);
         for (int cls = base / g; cls * g < end; ++cls) {

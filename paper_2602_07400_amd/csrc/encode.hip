@@ -6,25 +6,26 @@
 //
 // Two kernels, one lane per sample and one wave per 64-sample column in both:
 //
-// k_encode_t (b <= 8, the hot path).  A block first fills an LDS code table
-// code[f][v] = sum_t (v > theta[f][t]) << t for its tile of features and every
-// pixel value v, then reuses it for several tiles of 16 columns (1024
-// samples); each wave packs 4 of the 16 columns, one at a time (at small
-// batches 2 or 4 blocks share a tile's columns, down to one per wave, so that
-// more blocks share the latency).  The table is
-// built four codes per thread at a time: a dword holds the codes of four
-// consecutive values, and threshold t sets its bit from the first value above
-// it on.  A lane loads
-// its own sample's FT feature bytes (16-byte loads where rows and tiles allow;
-// the next column's bytes are in flight while the current one is packed) and
-// assembles, for a group of floor(64/b) features (8 at b = 7, 16 at b = 3),
-// the 64-bit row of its sample's wires (one table read and one
-// shift-or per feature), and a 64x64 bit transpose across the wave
-// (v_permlane32_swap for the 32-lane halves, then five ds_swizzle xor stages,
-// each a rotate (v_alignbit) and a bit-field merge (v_bfi) per register) turns
-// rows of samples into packed words of wires: lane p ends with wire p's word.
-// The words of a 16-column tile are collected in LDS and written as whole
-// 128-byte row segments.
+// k_encode_t (b <= 8, the hot path).  A block owns a tile of features and
+// packs one or two tiles of 16 columns (1024 samples) of them; each wave packs 4
+// of the 16 columns, one at a time (at small batches 2 or 4 blocks share a
+// tile's columns, down to one per wave, so that more blocks share the latency).
+// A lane loads its own sample's feature bytes (16-byte loads where rows and
+// tiles allow; the next column's bytes are in flight while the current one is
+// packed) and compares them four at a time as bytes of a register
+// (row_thermometer) into the 64-bit row of its sample's wires, and a 64x64 bit
+// transpose across the wave (v_permlane32_swap for the 32-lane halves, then
+// five ds_swizzle xor stages) turns rows of samples into packed words of wires:
+// lane p ends with the word of wire row_wire(p).  The words of a 16-column tile
+// are collected in LDS and written as whole 128-byte row segments.
+//
+// What bounds it: at large batches the pixel lines and the stores (1.51 GB at
+// 2^18 x 3072, b = 7, in 367 us, 4.1 TB/s; torch copies at 4.8 on the same
+// card), whatever the packing costs: with the codes looked up in an LDS table
+// per block it took the same 367 us there, but 340 and 364 at b = 5 and 6
+// against 307 and 339 now.  Small batches are latency, where the table's build
+// and its lookups were a third: 16384 x 784 at b = 7 14.7 -> 9.1 us, 8192 x 3072
+// at b = 3 16.5 -> 8.7, 65536 x 3072 at b = 3 59 -> 49.
 //
 // k_encode_ballot (any b <= 64).  Each comparison is a wave64 ballot, i.e. the
 // packed word of one wire; v_writelane collects 64 such words into one lane
@@ -34,8 +35,8 @@
 // slab layout [Wp/S][wires][S] of bitlogic_forward's intermediates.
 //
 // The binary-coded uniform fixed-point encoder (Sec. 3 "Encoders and heads":
-// 2^b levels on b wires; Sec. 5 "Encoder") is the same kernel with another
-// code table: code[f][v] = round(v (2^b - 1) / 255), wire t = bit t.
+// 2^b levels on b wires; Sec. 5 "Encoder") is the same kernel with another row
+// (row_binary): round(v (2^b - 1) / 255), wire t = bit t.
 #include "bl_device.h"
 
 namespace bl {
@@ -62,22 +63,97 @@ __device__ __forceinline__ int64_t out_index(int64_t wire, int64_t wb, int64_t W
         return wire * W + wb;
 }
 
-template <int B>
+template <int B, int KG>
 struct EncGeom {
-    // Features per 64-wire group: floor(64 / B), except at B = 7 and 3, which
-    // take 8 and 16 (56 and 48 of the 64 wires) so that a tile is a whole
-    // number of 16-byte pieces and four or two tiles share each 128-byte
-    // pixel line, instead of 36- or 84-byte tiles straddling lines (encoder
-    // 8-17% faster on 256K-1M samples x 784-3072 features, the transpose
-    // then carries 8 or 16 idle rows).
-    static constexpr int kFPG = (B == 7) ? 8 : (B == 3) ? 16 : 64 / B;
-    static_assert(kFPG * B <= 64, "a group's wires fit one 64-bit row");
+    // Features per 64-wire group, in quads whose four bytes are compared at
+    // once; at B = 3 and 6 fewer quads than would fit, so that a tile is a
+    // whole number of 16-byte pieces and shares 128-byte pixel lines with its
+    // neighbours instead of straddling them.
+    static constexpr int kQ = (B == 3) ? 4 : 16 / B;     // quads per group
+    static constexpr int kFPG = 4 * kQ;                  // features per group
+    static constexpr int kS = kQ * B;                    // (quad, wire) slots per group
+    static_assert(kS <= 16, "a group's wires fit one 64-bit row");
     static constexpr int kWPG = kFPG * B;                // wires per group (<= 64)
-    static constexpr int kG = (B <= 2) ? 1 : (B == 4) ? 2 : (B == 5) ? 3 : 4;
+    static constexpr int kG = KG;                        // groups per tile
     static constexpr int kFT = kFPG * kG;                // features per tile
     static constexpr int kDw = kFT / 4;                  // pixel dwords per sample
-    static_assert(kFT % 4 == 0, "feature tile must be whole dwords");
 };
+
+// The wire bits of a group of features of one sample, as a 64-bit row: slot
+// k = quad * B + t puts bit t of the quad's four features at bits 7 - k % 8,
+// 15 - k % 8, ... of half k / 8.  Thermometer: byte x is above byte th exactly
+// where x + ~th carries out of the byte, the majority of x, ~th and the sum of
+// their low 7 bits at bit 7; four comparisons in three instructions (and, add,
+// v_bitop3), two more to place them, all of the full-rate kind.  Binary code:
+// round(v (2^B - 1) / 255) = (t + (t >> 8)) >> 8 with t = v (2^B - 1) + 128,
+// two features per register.
+template <int B>
+__device__ __forceinline__ void place_slot(int k, uint32_t r, const uint32_t (&mk)[8],
+                                           uint32_t &lo, uint32_t &hi)
+{
+    uint32_t &row = k < 8 ? lo : hi;
+    // row | (r & mk): v_bitop3 with the mask in a VGPR
+    row = __builtin_amdgcn_bitop3_b32(row, r, mk[k % 8], 0xF8);
+}
+
+template <int B>
+__device__ __forceinline__ void row_thermometer(const uint32_t *px, const uint32_t *s_nt,
+                                                const uint32_t (&mk)[8], uint32_t &lo,
+                                                uint32_t &hi)
+{
+    using G = EncGeom<B, 1>;
+    lo = hi = 0;
+    // read here, not kept over the column loop: the registers that all groups'
+    // thresholds would take cost a wave per SIMD
+    asm volatile("" ::: "memory");
+    uint32_t nt[16];
+#pragma unroll
+    for (int q = 0; q < (G::kS + 3) / 4; ++q) {
+        const u32x4 v = reinterpret_cast<const u32x4 *>(s_nt)[q];
+        nt[4 * q] = v.x;
+        nt[4 * q + 1] = v.y;
+        nt[4 * q + 2] = v.z;
+        nt[4 * q + 3] = v.w;
+    }
+#pragma unroll
+    for (int k = 0; k < G::kS; ++k) {
+        const uint32_t v = px[k / B];
+        const uint32_t z = (v & 0x7F7F7F7Fu) + (nt[k] & 0x7F7F7F7Fu);
+        place_slot<B>(k, __builtin_amdgcn_bitop3_b32(v, nt[k], z, 0xE8) >> (k % 8), mk, lo, hi);
+    }
+}
+
+template <int B>
+__device__ __forceinline__ void row_binary(const uint32_t *px, const uint32_t (&mk)[8],
+                                           uint32_t &lo, uint32_t &hi)
+{
+    using G = EncGeom<B, 1>;
+    lo = hi = 0;
+#pragma unroll
+    for (int q = 0; q < G::kQ; ++q) {
+        auto code = [](uint32_t v) {             // bytes 0 and 2 of v
+            const uint32_t t = (v << B) - v + 0x00800080u;
+            return ((t + ((t >> 8) & 0x00FF00FFu)) >> 8) & 0x00FF00FFu;
+        };
+        const uint32_t c = code(px[q] & 0x00FF00FFu) | code((px[q] >> 8) & 0x00FF00FFu) << 8;
+#pragma unroll
+        for (int t = 0; t < B; ++t) {
+            const int k = q * B + t;
+            // bit t of each byte to bit 7 - k % 8
+            place_slot<B>(k, __builtin_amdgcn_alignbit(c, c, (t - 7 + k % 8 + 32) % 32), mk, lo,
+                          hi);
+        }
+    }
+}
+
+// The wire (within its group) whose column lane p holds after the transpose, or
+// -1 for an idle row bit.
+template <int B>
+__device__ __forceinline__ int row_wire(int p)
+{
+    const int slot = p / 32 * 8 + 7 - p % 8;
+    return slot < EncGeom<B, 1>::kS ? (slot / B * 4 + p % 32 / 8) * B + slot % B : -1;
+}
 
 constexpr int kEncCols = 16;     // columns per output tile: 128-byte row segments
 constexpr int kOtRow = kEncCols + 1;   // LDS words per tile row (odd: no bank conflicts)
@@ -150,16 +226,15 @@ __device__ __forceinline__ void load_pixels(const uint8_t *__restrict__ x, int64
     }
 }
 
-template <int B, int LAYOUT, int CS>
+template <int B, int LAYOUT, int KG, int CS>
 __global__ __launch_bounds__(kThreads) void k_encode_t(
     const uint8_t *__restrict__ x, int64_t n, int32_t d, const uint8_t *__restrict__ th,
     uint64_t *__restrict__ out, int64_t W, int64_t W_cols, int32_t n_ftiles,
     int32_t tiles_per_block, int64_t n_tiles, int64_t n_tgroups, int vec16, int kind)
 {
-    using G = EncGeom<B>;
+    using G = EncGeom<B, KG>;
     constexpr int kWires = G::kG * G::kWPG;              // wire rows of one output tile
-    __shared__ __attribute__((aligned(4))) uint8_t lut[G::kFT * 256];
-    __shared__ uint8_t ths[G::kFT * B];
+    __shared__ __attribute__((aligned(16))) uint32_t s_nt[G::kG][16];
     __shared__ uint64_t otile[kWires * kOtRow];
 
     int tg, ft;
@@ -179,38 +254,27 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
 
-    // ---- code table for this feature tile: dword e holds the codes of values
-    // 4*(e%64) .. +3 of tile feature e/64 (one feature per wave); bit t of a
-    // code is set from byte position p on, p = clamp(theta_t - v0 + 1, 0, 4)
-    if (kind == kEncThermometer)
-        for (int q = threadIdx.x; q < nf * B; q += kThreads)
-            ths[q] = th[(int64_t)f0 * B + q];
-    __syncthreads();
-    for (int e = threadIdx.x; e < G::kFT * 64; e += kThreads) {
-        const int f = e >> 6;
-        const int v0 = 4 * (e & 63);
-        uint32_t codes = 0;
-        if (f < nf && kind == kEncThermometer) {
-#pragma unroll
-            for (int t = 0; t < B; ++t) {
-                const int p = min(max((int)ths[f * B + t] - v0 + 1, 0), 4);
-                const uint32_t m = (p >= 4) ? 0u : (0xFFFFFFFFu << (8 * p));
-                codes |= m & (0x01010101u << t);
-            }
-        } else if (f < nf) {
-            // binary code: q = round(v (2^B - 1) / 255), no ties since 255 is odd
+    // complements of the tile's thresholds, a dword per quad and wire (a
+    // feature past the row gets 255, which nothing is above)
+    if (kind == kEncThermometer) {
+        for (int e = threadIdx.x; e < G::kG * G::kS; e += kThreads) {
+            const int f = e / G::kS * G::kFPG + e % G::kS / B * 4, t = e % G::kS % B;
+            uint32_t v = 0;
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                codes |= (uint32_t)((2u * (uint32_t)(v0 + u) * ((1u << B) - 1u) + 255u) / 510u)
-                         << (8 * u);
+                v |= (f + u < nf ? (uint32_t)th[(int64_t)(f0 + f + u) * B + t] : 255u) << (8 * u);
+            s_nt[e / G::kS][e % G::kS] = ~v;
         }
-        reinterpret_cast<uint32_t *>(lut)[e] = codes;
+        __syncthreads();
     }
-    __syncthreads();
-
-    // per-lane constants of the transpose stages
-    uint32_t amt[5], msk[5];
-    transpose_consts(lane, amt, msk);
+    uint32_t mk[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        mk[k] = 0x80808080u >> k;
+        asm volatile("" : "+v"(mk[k]));          // in VGPRs: full rate in v_bitop3
+    }
+    const dev::Transpose tr = transpose_consts(lane);
+    const int my_wire = row_wire<B>(lane);
 
     // block tg covers part (tg % CS) of the columns of tile group tg / CS:
     // cpb columns per tile, cpw consecutive columns per wave
@@ -243,25 +307,14 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
             }
 #pragma unroll
             for (int gi = 0; gi < G::kG; ++gi) {
-                uint32_t lo = 0, hi = 0;
-#pragma unroll
-                for (int fl = 0; fl < G::kFPG; ++fl) {
-                    const int f = gi * G::kFPG + fl;
-                    const uint32_t byte = (px[f / 4] >> (8 * (f % 4))) & 0xFFu;
-                    const uint32_t code = lut[f * 256 + byte];
-                    const int pos = fl * B;
-                    if (pos + B <= 32) {
-                        lo |= code << pos;
-                    } else if (pos >= 32) {
-                        hi |= code << (pos - 32);
-                    } else {
-                        lo |= code << pos;
-                        hi |= code >> (32 - pos);
-                    }
-                }
-                transpose64(lo, hi, amt, msk);
-                if (lane < G::kWPG)
-                    otile[(gi * G::kWPG + lane) * kOtRow + col] = ((uint64_t)hi << 32) | lo;
+                uint32_t lo, hi;
+                if (kind == kEncThermometer)
+                    row_thermometer<B>(px + gi * G::kQ, s_nt[gi], mk, lo, hi);
+                else
+                    row_binary<B>(px + gi * G::kQ, mk, lo, hi);
+                transpose64(lo, hi, tr);
+                if (my_wire >= 0)
+                    otile[(gi * G::kWPG + my_wire) * kOtRow + col] = ((uint64_t)hi << 32) | lo;
             }
             if (more) {
 #pragma unroll
@@ -374,43 +427,67 @@ __global__ __launch_bounds__(kThreads) void k_encode_ballot(
     }
 }
 
+// Groups per tile: 32 to 64 features where the batch gives kEncBigBlocks blocks
+// of them; half of that below, for more blocks and a shorter chain in each
+// (16384 x 784 at b = 7 13.7 -> 9.1 us; a quarter: 10.6; at 4096 blocks the big
+// tiles win, 131072 x 784 at b = 7 43.8 against 46.4 us, and at 2^18 x 3072 368
+// against 420, since more blocks share each pixel line).
+constexpr int64_t kEncBigBlocks = 2048;
+template <int B>
+constexpr int big_groups()
+{
+    return B <= 2 ? 1 : B == 4 ? 2 : 4;
+}
+template <int B>
+constexpr int small_groups()
+{
+    return big_groups<B>() < 2 ? 1 : 2;
+}
+
+template <int B, int LAYOUT, int KG, int CS>
+hipError_t launch_tile(const uint8_t *x, int64_t n, int32_t d, const uint8_t *th, uint64_t *out,
+                       int64_t W_cols, int kind, int64_t tpb, hipStream_t stream)
+{
+    using G = EncGeom<B, KG>;
+    const int64_t W = (n + 63) / 64;
+    const int64_t n_tiles = (W_cols + kEncCols - 1) / kEncCols;
+    const int32_t n_ftiles = (d + G::kFT - 1) / G::kFT;
+    const int64_t n_tg = (n_tiles + tpb - 1) / tpb * CS;
+    const int64_t blocks = dealt_blocks(n_tg, n_ftiles);
+    if (blocks > 0x7fffffff)
+        return hipErrorInvalidConfiguration;
+    const int vec16 = (d % 16 == 0) && ((uintptr_t)x % 16 == 0) && G::kFT % 16 == 0;
+    hipLaunchKernelGGL((k_encode_t<B, LAYOUT, KG, CS>), dim3((unsigned)blocks), dim3(kThreads), 0,
+                       stream, x, n, d, th, out, W, W_cols, n_ftiles, (int32_t)tpb, n_tiles, n_tg,
+                       vec16, kind);
+    return hipGetLastError();
+}
+
 template <int B, int LAYOUT>
 hipError_t launch_t(const uint8_t *x, int64_t n, int32_t d, const uint8_t *th, uint64_t *out,
                     int64_t W_cols, int kind, hipStream_t stream)
 {
-    using G = EncGeom<B>;
-    const int64_t W = (n + 63) / 64;
+    constexpr int KB = big_groups<B>(), KS = small_groups<B>();
     const int64_t n_tiles = (W_cols + kEncCols - 1) / kEncCols;
-    const int32_t n_ftiles = (d + G::kFT - 1) / G::kFT;
-    // enough blocks to fill the chip; at most BL_ENC_TPB column tiles reuse one
-    // code table (longer runs let the blocks that share pixel lines drift
+    const int64_t big = n_tiles * ((d + EncGeom<B, KB>::kFT - 1) / EncGeom<B, KB>::kFT);
+    // enough blocks to fill the chip; at most BL_ENC_TPB column tiles share one
+    // block's constants (longer runs let the blocks that share pixel lines drift
     // apart, and the lines are fetched again: 2 tiles a block beat 1, 3, 4
     // and 8 on 256K-1M samples x 784-3072 features)
-    int64_t tpb = n_tiles * n_ftiles / 2048;
-    tpb = tpb < 1 ? 1 : (tpb > BL_ENC_TPB ? BL_ENC_TPB : tpb);
-    // small batches: split each tile's 16 columns over 2 or 4 blocks (down to
-    // one column per wave), so that more blocks share the latency
-    int32_t csplit = 1;
-    while (csplit < 4 && n_tiles * n_ftiles * csplit < 1024)
-        csplit *= 2;
-    const int64_t n_tg = (n_tiles + tpb - 1) / tpb * csplit;
-    const int64_t blocks = dealt_blocks(n_tg, n_ftiles);
-    if (blocks > 0x7fffffff)
-        return hipErrorInvalidConfiguration;
-    const int vec16 = (d % 16 == 0) && ((uintptr_t)x % 16 == 0);
-    if (csplit == 4)
-        hipLaunchKernelGGL((k_encode_t<B, LAYOUT, 4>), dim3((unsigned)blocks), dim3(kThreads), 0,
-                           stream, x, n, d, th, out, W, W_cols, n_ftiles, (int32_t)tpb, n_tiles,
-                           n_tg, vec16, kind);
-    else if (csplit == 2)
-        hipLaunchKernelGGL((k_encode_t<B, LAYOUT, 2>), dim3((unsigned)blocks), dim3(kThreads), 0,
-                           stream, x, n, d, th, out, W, W_cols, n_ftiles, (int32_t)tpb, n_tiles,
-                           n_tg, vec16, kind);
-    else
-        hipLaunchKernelGGL((k_encode_t<B, LAYOUT, 1>), dim3((unsigned)blocks), dim3(kThreads), 0,
-                           stream, x, n, d, th, out, W, W_cols, n_ftiles, (int32_t)tpb, n_tiles,
-                           n_tg, vec16, kind);
-    return hipGetLastError();
+    if (big >= kEncBigBlocks) {
+        int64_t tpb = big / kEncBigBlocks;
+        tpb = tpb < 1 ? 1 : (tpb > BL_ENC_TPB ? BL_ENC_TPB : tpb);
+        return launch_tile<B, LAYOUT, KB, 1>(x, n, d, th, out, W_cols, kind, tpb, stream);
+    }
+    // small batches: tiles of fewer features, and each tile's 16 columns split
+    // over 2 or 4 blocks (down to one column per wave), so that more blocks
+    // share the latency
+    const int64_t small = n_tiles * ((d + EncGeom<B, KS>::kFT - 1) / EncGeom<B, KS>::kFT);
+    if (2 * small < 1024)
+        return launch_tile<B, LAYOUT, KS, 4>(x, n, d, th, out, W_cols, kind, 1, stream);
+    if (small < 1024)
+        return launch_tile<B, LAYOUT, KS, 2>(x, n, d, th, out, W_cols, kind, 1, stream);
+    return launch_tile<B, LAYOUT, KS, 1>(x, n, d, th, out, W_cols, kind, 1, stream);
 }
 
 template <int LAYOUT>
