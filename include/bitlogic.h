@@ -192,7 +192,8 @@ int bitlogic_forward(const uint8_t *x, int64_t n_samples, int32_t n_features,
                      void *workspace, size_t workspace_bytes, void *stream);
 
 /* bitlogic_forward plus stage timing, for profiling: the same kernels on the
- * same stream, and hipEventRecord(events[i], stream) at every stage boundary:
+ * same stream (but for the smallest batches and networks, which bitlogic_forward
+ * runs as one kernel and this one stage by stage), and hipEventRecord(events[i], stream) at every stage boundary:
  * events[0] before the encoder, events[1] after it, events[1 + l] after
  * layer l (l = 1..n_layers), events[n_layers + 2] after the head.
  * `events` is a host array of n_events = n_layers + 3 hipEvent_t handles

@@ -140,6 +140,7 @@ struct ForwardPlan {
     uint64_t jump_mask;    // bit l: layer l runs on the node-per-wave kernel
     size_t off_rec;        // its per-node records (shared by those layers)
     bl::ColumnHeadPlan cols;   // cols.ok: the column kernels run the batch
+    bl::ColumnNetwork net;     // net.ok: and a column's network runs in one block
 };
 
 bitlogic_network legacy_net(int32_t n_features, const uint8_t *thresholds, int32_t n_thresholds,
@@ -240,6 +241,15 @@ int plan_forward(int64_t n, int32_t d, int32_t b, const bitlogic_layer *layers, 
     fp->cols.ok = fp->cols.ok && L >= 2 && b <= 8 && fp->fused && jm == kJumpAuto &&
                   (size_t)n * c * sizeof(int32_t) <= enc &&
                   column_cost(fp->W, d * b, layers, L) <= kColumnMaxCost;
+    fp->net.ok = false;
+    if (fp->cols.ok && L <= bl::kColumnMaxLayers) {
+        int32_t w[bl::kColumnMaxLayers], k[bl::kColumnMaxLayers];
+        for (int32_t l = 0; l < L; ++l) {
+            w[l] = layers[l].w_out;
+            k[l] = layers[l].k;
+        }
+        fp->net = bl::plan_column_network(d, b, w, k, L, c, n);
+    }
     fp->off_rec = fp->off_head + round_up(fp->head.ws_bytes);
     fp->total = fp->off_rec + (fp->jump_mask ? round_up(bl::jump_records_bytes(rec_w)) : 0);
     return BITLOGIC_OK;
@@ -380,16 +390,34 @@ int plan_network(const bitlogic_network *net, int64_t n, ForwardPlan *fp)
 template <class Mark>
 int forward_columns(const bitlogic_network *net, const ForwardPlan &fp, const uint8_t *x,
                     int64_t n, int32_t *scores, int32_t *argmax, uint64_t *enc,
-                    uint64_t *const (&act)[2], hipStream_t s, Mark mark)
+                    uint64_t *const (&act)[2], hipStream_t s, bool timed, Mark mark)
 {
     const bitlogic_layer *layers = net->layers;
     const int32_t L = net->n_layers, c = net->n_classes;
+    const int kind = net->encoder == BITLOGIC_ENCODER_BINARY ? bl::kEncBinary
+                                                             : bl::kEncThermometer;
+    const bool dsp = net->head == BITLOGIC_HEAD_GROUPED_DSP;
+    // the counts: the caller's scores, or scratch where they are not wanted
+    int32_t *counts = !dsp && scores ? scores : reinterpret_cast<int32_t *>(enc);
     hipError_t e = mark(0);
+    // one kernel for the whole network where a column fits a block; a timed
+    // forward has stages to tell apart
+    if (e == hipSuccess && !timed && fp.net.ok) {
+        bl::ColumnNetwork cn = fp.net;
+        for (int32_t l = 0; l < L; ++l) {
+            cn.conn[l] = layers[l].conn;
+            cn.tables[l] = layers[l].tables;
+        }
+        e = bl::launch_column_network(x, n, net->n_features, net->thresholds, net->n_bits, kind,
+                                      cn, c, !dsp && !scores ? nullptr : counts,
+                                      dsp ? nullptr : argmax, s);
+        if (e == hipSuccess && dsp)
+            e = bl::launch_grouped_dsp(counts, n, c, net->head_weights, scores, argmax, s);
+        return hip_status(e, "forward: network launch");
+    }
     if (e == hipSuccess)
         e = bl::launch_column_encode(x, n, net->n_features, net->thresholds, net->n_bits, enc,
-                                     net->encoder == BITLOGIC_ENCODER_BINARY ? bl::kEncBinary
-                                                                             : bl::kEncThermometer,
-                                     s);
+                                     kind, s);
     if (e == hipSuccess)
         e = mark(1);
     if (e != hipSuccess)
@@ -406,9 +434,6 @@ int forward_columns(const bitlogic_network *net, const ForwardPlan &fp, const ui
         cur = act[l & 1];
         w_in = layers[l].w_out;
     }
-    const bool dsp = net->head == BITLOGIC_HEAD_GROUPED_DSP;
-    // the counts: the caller's scores, or scratch where they are not wanted
-    int32_t *counts = !dsp && scores ? scores : reinterpret_cast<int32_t *>(enc);
     e = bl::launch_column_head(cur, w_in, layers[L - 1].conn, layers[L - 1].tables,
                                layers[L - 1].w_out, layers[L - 1].k, c, n, fp.cols, counts,
                                dsp ? nullptr : argmax, s);
@@ -464,7 +489,8 @@ int forward_impl(const bitlogic_network *net, const uint8_t *x, int64_t n_sample
     uint64_t *act[2] = {reinterpret_cast<uint64_t *>(ws + fp.off_a),
                         reinterpret_cast<uint64_t *>(ws + fp.off_b)};
     if (fp.cols.ok)
-        return forward_columns(net, fp, x, n_samples, scores, argmax, enc, act, s, mark);
+        return forward_columns(net, fp, x, n_samples, scores, argmax, enc, act, s,
+                               events != nullptr, mark);
     hipError_t e = mark(0);
     if (e == hipSuccess)
         e = bl::launch_encode(x, n_samples, net->n_features, net->thresholds, net->n_bits, enc,

@@ -196,6 +196,22 @@ struct ColumnHeadPlan {
     size_t lds;
 };
 ColumnHeadPlan plan_column_head(int32_t w_in, int32_t w_out, int32_t c);
+// A network whose column runs in one block (ok): its layers and the LDS it takes
+// (rows of the two activation buffers, bytes in all).
+constexpr int kColumnMaxLayers = 4;
+struct ColumnNetwork {
+    bool ok;
+    int32_t n_layers, rows_a, rows_b;
+    int32_t w[kColumnMaxLayers], k[kColumnMaxLayers];
+    const int32_t *conn[kColumnMaxLayers];
+    const uint64_t *tables[kColumnMaxLayers];
+    size_t lds;
+};
+ColumnNetwork plan_column_network(int32_t d, int32_t b, const int32_t *w, const int32_t *k,
+                                  int32_t n_layers, int32_t c, int64_t n);
+hipError_t launch_column_network(const uint8_t *x, int64_t n, int32_t d, const uint8_t *th,
+                                 int32_t b, int kind, const ColumnNetwork &net, int32_t c,
+                                 int32_t *counts, int32_t *argmax, hipStream_t stream);
 hipError_t launch_column_encode(const uint8_t *x, int64_t n, int32_t d, const uint8_t *th,
                                 int32_t b, uint64_t *out, int kind, hipStream_t stream);
 hipError_t launch_column_layer(const uint64_t *in, int32_t w_in, int32_t W, const int32_t *conn,

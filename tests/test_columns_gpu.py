@@ -1,5 +1,6 @@
 """Small batches, which run by 64-sample columns, against the oracle and against
-the slab kernels (an environment switch keeps those): one to many columns and
+the slab kernels (an environment switch keeps those), in one block a column and
+stage by stage: one to many columns and
 nodes a lane, ragged batches, every encoder width and fan-in, heads whose
 classes sit in one block or several, groups smaller than a wave and larger than
 a block's rounds, inputs staged in LDS and not, and both class heads."""
@@ -48,6 +49,15 @@ def check(monkeypatch, n, d, b, widths, k, c, dsp=False, binary=False, seed=0):
         assert np.array_equal(out.cpu().numpy(), want), switch
         assert np.array_equal(am.cpu().numpy(), best), switch
         assert np.array_equal(only.cpu().numpy(), best), switch
+        # with stage events the stages are kernels of their own
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(layers) + 3)]
+        for e in ev:
+            e.record()
+        out, am = model.forward(xd, workspace=ws, events=ev)
+        torch.cuda.synchronize()
+        assert all(ev[i].elapsed_time(ev[i + 1]) >= 0 for i in range(len(layers) + 2))
+        assert np.array_equal(out.cpu().numpy(), want), switch
+        assert np.array_equal(am.cpu().numpy(), best), switch
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1000])
@@ -81,20 +91,8 @@ def test_shapes(monkeypatch, n, widths, k, c):
         check(monkeypatch, n, 40, 3, widths, k, c, dsp=True, seed=1)
 
 
-def test_stage_events():
-    rng = np.random.default_rng(5)
-    layers, w_in = [], 80
-    for w in (100, 90):
-        layers.append((draw_connectivity(rng, w, 4, w_in),
-                       rng.integers(0, 1 << 16, size=w, dtype=np.uint64)))
-        w_in = w
-    th = rng.integers(0, 256, size=(40, 2), dtype=np.uint8)
-    x = rng.integers(0, 256, size=(100, 40), dtype=np.uint8)
-    model = bl.BitlogicModel.from_numpy(th, layers, 10, device=DEV)
-    ev = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
-    for e in ev:
-        e.record()
-    out, _ = model.forward(torch.from_numpy(x).to(DEV), events=ev)
-    torch.cuda.synchronize()
-    assert all(ev[i].elapsed_time(ev[i + 1]) >= 0 for i in range(4))
-    assert np.array_equal(out.cpu().numpy(), oracle.forward(x, th, layers, 10)[0])
+
+@pytest.mark.parametrize("widths,c", [((1000, 900, 800, 700), 10), ((60, 70, 80, 90, 100), 5),
+                                      ((1025, 1024, 1030), 206)])
+def test_depths_in_one_block_and_deeper(monkeypatch, widths, c):
+    check(monkeypatch, 300, 50, 2, widths, [2, 6, 1, 3, 5][:len(widths)], c)
