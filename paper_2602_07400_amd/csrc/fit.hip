@@ -10,32 +10,36 @@
 // cum(v) / total >= i / (b + 1) -- and every feature of the group receives
 // the group's ladder.
 //
-// k_fit_hist: each block counts a run of rows into an LDS histogram per
-// group (LDS atomics), then adds it into the global 64-bit histogram.  The
-// LDS histogram holds R interleaved copies of every bin (lane l counts into
-// copy l mod R, at word bin * R + l mod R), so that the 64 atomics of a wave
-// spread over the banks and rarely hit the same word; the copies are summed
-// before the global add.  Rows are read as coalesced dwords: a thread keeps
-// its columns (and their groups) and walks the rows, kRowUnroll rows' loads
-// at a time.  k_fit_select:
-// one block per group turns the histogram into the ladder (a block prefix sum,
-// one thread per bin).
+// k_fit_hist: each block counts a run of rows into an LDS histogram per group
+// (LDS atomics), then adds it into the global 64-bit histogram.  The LDS
+// histogram holds R interleaved copies of every bin (lane l counts into copy l
+// mod R, at word bin * R + l mod R); at R = 32, which up to 4 groups get, the 32
+// lanes of half a wave fall into 32 banks, whatever the pixels.  The copies are
+// summed before the global add.  A thread keeps a 16-byte column of the rows,
+// with its bytes' groups, and walks the rows of its place in the block,
+// kRowUnroll rows' loads at a time, at any alignment; the last column of rows
+// that are no whole number of them starts earlier and counts only its own
+// bytes.  k_fit_select: one block per group turns the histogram into the ladder
+// (a block prefix sum, one thread per bin).
+//
+// What bounds it: the LDS atomics (about 11 lanes a clock and CU) at large
+// batches, 805 MB in three groups in 148 us with all three launches (163 with
+// 16 copies, dword columns and 1024 blocks of 256 threads), the global adds of
+// the histograms at small ones: one round of 1024-thread blocks instead of 1024
+// blocks took 25 MB from 38 to 21 us and 0.25 MB from 29 to 21; rows that are not
+// whole dwords no longer go a byte per load (100000 x 2001 74 -> 43 us).  Two rows
+// in flight a thread were as fast as 4 and 3-7% faster than 8.
 #include "bl_internal.h"
 
 namespace bl {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kHistBlocks = 1024;
-#ifndef BL_FIT_UNROLL
-#define BL_FIT_UNROLL 32
-#endif
-#ifndef BL_FIT_MAX_REP
-#define BL_FIT_MAX_REP 32
-#endif
-constexpr int kRowUnroll = BL_FIT_UNROLL;
-constexpr int kFitMaxRep = BL_FIT_MAX_REP;        // copies of each histogram bin
-constexpr int kFitHistBytes = 48 << 10;           // LDS of one histogram block
+constexpr int kHistThreads = 1024;
+constexpr int kRowUnroll = 2;
+constexpr int kFitMaxRep = 32;                    // copies of each histogram bin
+constexpr int kFitHistBytes = 128 << 10;          // LDS of one histogram block
+constexpr int kColBytes = 16;                     // pixels of a thread's column
 
 __global__ __launch_bounds__(kThreads) void k_fit_clear(uint64_t *__restrict__ ws, int32_t n)
 {
@@ -44,70 +48,84 @@ __global__ __launch_bounds__(kThreads) void k_fit_clear(uint64_t *__restrict__ w
         ws[i] = 0;
 }
 
-__global__ __launch_bounds__(kThreads) void k_fit_hist(
+__global__ __launch_bounds__(kHistThreads) void k_fit_hist(
     const uint8_t *__restrict__ x, int64_t n, int32_t d, int32_t per, int32_t n_groups,
-    int64_t rows_per_block, int aligned4, int32_t rep_log2, uint64_t *__restrict__ ws)
+    int64_t rows_per_block, int32_t rep_log2, uint64_t *__restrict__ ws)
 {
     extern __shared__ uint32_t hist[];             // [n_groups][256][R], R = 2^rep_log2
     const int nbins = n_groups * 256;
-    for (int i = threadIdx.x; i < nbins << rep_log2; i += kThreads)
+    for (int i = threadIdx.x; i < nbins << rep_log2; i += kHistThreads)
         hist[i] = 0;
     __syncthreads();
     const uint32_t copy = threadIdx.x & ((1u << rep_log2) - 1);
-    // LDS word of bin (g256 + v) in this lane's copy
-    auto slot = [&](int g256, uint32_t v) { return (((uint32_t)g256 + v) << rep_log2) + copy; };
     const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
     const int64_t r1 = min(n, r0 + rows_per_block);
-    if (aligned4) {
-        const int32_t d4 = d / 4;
-        const uint32_t *x32 = reinterpret_cast<const uint32_t *>(x);
-        for (int32_t fq = threadIdx.x; fq < d4; fq += kThreads) {
-            int g[4];
+    if (d >= kColBytes) {
+        // columns of 16 bytes; up to kHistThreads of them side by side, as many
+        // rows at once as fit beside
+        const int n_cols = (d + kColBytes - 1) / kColBytes;
+        const int wide = min(n_cols, kHistThreads);
+        const int tall = kHistThreads / wide;
+        const int rt = threadIdx.x / wide;
+        for (int c0 = 0; c0 < n_cols; c0 += wide) {
+            const int c = c0 + threadIdx.x - rt * wide;
+            if (rt >= tall || c >= n_cols)
+                continue;
+            const int off = min(c * kColBytes, d - kColBytes);
+            const int first = c * kColBytes - off;       // bytes the column before counts
+            uint32_t base[kColBytes];                    // word of bin 0 of each byte's group
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                g[u] = (4 * fq + u) / per * 256;
-            // eight rows' loads in flight before their counts
-            int64_t r = r0;
-            for (; r + kRowUnroll <= r1; r += kRowUnroll) {
-                uint32_t v[kRowUnroll];
+            for (int u = 0; u < kColBytes; ++u)
+                base[u] = ((uint32_t)((off + u) / per * 256) << rep_log2) + copy;
+            // the bytes before `first` count as zeros, taken back below
+            u32x4 own;
 #pragma unroll
-                for (int q = 0; q < kRowUnroll; ++q)
-                    v[q] = x32[(r + q) * d4 + fq];
-#pragma unroll
-                for (int q = 0; q < kRowUnroll; ++q)
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        atomicAdd(&hist[slot(g[u], (v[q] >> (8 * u)) & 0xFFu)], 1u);
+            for (int q = 0; q < 4; ++q) {
+                const int drop = min(max(first - 4 * q, 0), 4);
+                own[q] = drop == 4 ? 0u : ~0u << (8 * drop);
             }
-            for (; r < r1; ++r) {
-                const uint32_t v = x32[r * d4 + fq];
+            auto count = [&](u32x4 v) {
+                v &= own;
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    atomicAdd(&hist[slot(g[u], (v >> (8 * u)) & 0xFFu)], 1u);
+                for (int u = 0; u < kColBytes; ++u)
+                    atomicAdd(&hist[base[u] + (((v[u / 4] >> (8 * (u % 4))) & 0xFFu) << rep_log2)],
+                              1u);
+            };
+            const uint8_t *src = x + off;
+            int64_t r = r0 + rt;
+            for (; r + (kRowUnroll - 1) * tall < r1; r += kRowUnroll * tall) {
+                u32x4 v[kRowUnroll];
+#pragma unroll
+                for (int q = 0; q < kRowUnroll; ++q)
+                    __builtin_memcpy(&v[q], src + (r + q * tall) * d, sizeof v[q]);
+#pragma unroll
+                for (int q = 0; q < kRowUnroll; ++q)
+                    count(v[q]);
+            }
+            for (; r < r1; r += tall) {
+                u32x4 v;
+                __builtin_memcpy(&v, src + r * d, sizeof v);
+                count(v);
+            }
+            if (first > 0 && r0 + rt < r1) {
+                const uint32_t rows = (uint32_t)((r1 - r0 - rt + tall - 1) / tall);
+#pragma unroll
+                for (int u = 0; u < kColBytes; ++u)
+                    if (u < first)
+                        atomicSub(&hist[base[u]], rows);
             }
         }
     } else {
-        for (int32_t f = threadIdx.x; f < d; f += kThreads) {
-            const int g = f / per * 256;
-            int64_t r = r0;
-            for (; r + kRowUnroll <= r1; r += kRowUnroll) {
-                uint32_t v[kRowUnroll];
-#pragma unroll
-                for (int q = 0; q < kRowUnroll; ++q)
-                    v[q] = x[(r + q) * d + f];
-#pragma unroll
-                for (int q = 0; q < kRowUnroll; ++q)
-                    atomicAdd(&hist[slot(g, v[q])], 1u);
-            }
-            for (; r < r1; ++r)
-                atomicAdd(&hist[slot(g, x[r * d + f])], 1u);
-        }
+        for (int64_t e = threadIdx.x; e < (r1 - r0) * d; e += kHistThreads)
+            atomicAdd(&hist[((uint32_t)((int)(e % d) / per * 256 + x[r0 * d + e]) << rep_log2) +
+                            copy],
+                      1u);
     }
     __syncthreads();
     // sum the copies (each thread starts at another copy, so that the
     // threads of a wave read different banks), then one global add per bin
     const int nrep = 1 << rep_log2;
-    for (int i = threadIdx.x; i < nbins; i += kThreads) {
+    for (int i = threadIdx.x; i < nbins; i += kHistThreads) {
         uint32_t sum = 0;
         for (int k = 0; k < nrep; ++k)
             sum += hist[((uint32_t)i << rep_log2) + ((uint32_t)(k + i) & (uint32_t)(nrep - 1))];
@@ -166,24 +184,24 @@ hipError_t launch_fit_quantiles(const uint8_t *x, int64_t n, int32_t d, int32_t 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    // rows per block: about kHistBlocks blocks, and a block's count of any
-    // one bin (at most rows * per) stays below 2^31
-    int64_t rows = (n + kHistBlocks - 1) / kHistBlocks;
+    // as many bin copies as the block's LDS budget allows (at least one)
+    int32_t rep_log2 = 0;
+    while ((2 << rep_log2) <= kFitMaxRep &&
+           (size_t)bins * sizeof(uint32_t) * (2u << rep_log2) <= (size_t)kFitHistBytes)
+        ++rep_log2;
+    const size_t lds = ((size_t)bins << rep_log2) * sizeof(uint32_t);
+    // one round of blocks: two a CU where their LDS allows, and a block's count
+    // of any one bin (at most rows * per) stays below 2^31
+    const int64_t want = 256 * (2 * lds <= (160 << 10) ? 2 : 1);
+    int64_t rows = (n + want - 1) / want;
     const int64_t cap = ((int64_t)1 << 31) / per;
     if (rows > cap)
         rows = cap < 1 ? 1 : cap;
     const int64_t blocks = (n + rows - 1) / rows;
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
-    const int aligned4 = (d % 4 == 0) && ((uintptr_t)x % 4 == 0);
-    // as many bin copies as the block's LDS budget allows (at least one)
-    int32_t rep_log2 = 0;
-    while ((2 << rep_log2) <= kFitMaxRep &&
-           (size_t)bins * sizeof(uint32_t) * (2u << rep_log2) <= (size_t)kFitHistBytes)
-        ++rep_log2;
-    hipLaunchKernelGGL(k_fit_hist, dim3((unsigned)blocks), dim3(kThreads),
-                       ((size_t)bins << rep_log2) * sizeof(uint32_t), stream, x, n, d, per,
-                       n_groups, rows, aligned4, rep_log2, ws);
+    hipLaunchKernelGGL(k_fit_hist, dim3((unsigned)blocks), dim3(kHistThreads), lds, stream, x, n,
+                       d, per, n_groups, rows, rep_log2, ws);
     e = hipGetLastError();
     if (e != hipSuccess)
         return e;
