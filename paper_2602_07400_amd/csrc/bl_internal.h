@@ -31,6 +31,17 @@ typedef u32x4 u32x4_a8 __attribute__((aligned(8)));
 constexpr int kLayoutRowMajor = 0;
 constexpr int kLayoutSlab = 1;
 
+// Whether a packed tensor of this size is stored non-temporally.  Smaller ones
+// are still in the 256 MB memory-side cache (and partly in the L2s) when the next
+// kernel reads them, which non-temporal stores give up: forwards of 50021 x 1021
+// through 9001, 7003 and 5005 nodes 128 -> 106 us, 262144 x 784 through 4000 and
+// 4000 218 -> 194, 30000 x 3072 through 20000 and 20000 91 -> 76.  Larger ones
+// only push the kernel's input out of the L2: 200000 x 784 through 8000 and 8000
+// (tensors of 137 and 200 MB) 342 -> 316 with the bound between the two, 342 with
+// it above both; 160000 x 3072 through 32000 and 32000 (640 MB) 919 against 931.
+constexpr int64_t kStreamBytes = (int64_t)160 << 20;
+inline bool streams_past_cache(int64_t bytes) { return bytes > kStreamBytes; }
+
 // Word (row r, column wb) of a packed tensor with `rows` rows in the slab
 // layout of bitlogic_forward's intermediates, [W / kSlabWords][rows][kSlabWords].
 __host__ __device__ inline int64_t slab_index(int64_t r, int64_t wb, int64_t rows)

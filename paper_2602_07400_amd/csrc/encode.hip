@@ -37,6 +37,8 @@
 // The binary-coded uniform fixed-point encoder (Sec. 3 "Encoders and heads":
 // 2^b levels on b wires; Sec. 5 "Encoder") is the same kernel with another row
 // (row_binary): round(v (2^b - 1) / 255), wire t = bit t.
+#include <type_traits>
+
 #include "bl_device.h"
 #include "encode_row.h"
 
@@ -49,9 +51,6 @@ constexpr int kThreads = 256;
 
 #ifndef BL_ENC_TPB
 #define BL_ENC_TPB 2
-#endif
-#ifndef BL_ENC_NT_STORE
-#define BL_ENC_NT_STORE 1
 #endif
 
 template <int LAYOUT>
@@ -130,7 +129,7 @@ template <int B, int LAYOUT, int KG, int CS>
 __global__ __launch_bounds__(kThreads) void k_encode_t(
     const uint8_t *__restrict__ x, int64_t n, int32_t d, const uint8_t *__restrict__ th,
     uint64_t *__restrict__ out, int64_t W, int64_t W_cols, int32_t n_ftiles,
-    int32_t tiles_per_block, int64_t n_tiles, int64_t n_tgroups, int vec16, int kind)
+    int32_t tiles_per_block, int64_t n_tiles, int64_t n_tgroups, int vec16, int kind, int nt)
 {
     using G = EncGeom<B, KG>;
     constexpr int kWires = G::kG * G::kWPG;              // wire rows of one output tile
@@ -235,30 +234,36 @@ __global__ __launch_bounds__(kThreads) void k_encode_t(
         __syncthreads();
         // write the tile: each wire's 16 words are one contiguous row segment
         const int64_t wb0 = tile * kEncCols;
-        for (int e = threadIdx.x; e < kWires * (cpb / 2); e += kThreads) {
-            const int r = e / (cpb / 2);                   // tile wire row
-            const int c2 = part * cpb + 2 * (e % (cpb / 2));   // even column
-            const int gi = r / G::kWPG, p = r % G::kWPG;
-            const int fg = gi * G::kFPG + p / B;           // feature of this wire in the tile
-            const int64_t wb = wb0 + c2;
-            if (fg < skip || fg >= nf || wb >= W_cols)
-                continue;
-            const int64_t wire = (int64_t)(f0 + gi * G::kFPG) * B + p;
-            const uint64_t w0 = otile[r * kOtRow + c2], w1 = otile[r * kOtRow + c2 + 1];
-            uint64_t *q = out + out_index<LAYOUT>(wire, wb, W, D0);
-            if (wb + 1 < W_cols && (LAYOUT == kLayoutSlab || ((uintptr_t)q % 16) == 0)) {
-                const u32x4 v = u32x4{(uint32_t)w0, (uint32_t)(w0 >> 32), (uint32_t)w1,
-                                      (uint32_t)(w1 >> 32)};
-                if (BL_ENC_NT_STORE)
-                    __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(q));
-                else
-                    *reinterpret_cast<u32x4 *>(q) = v;
-            } else {
-                q[0] = w0;
-                if (wb + 1 < W_cols)
-                    out[out_index<LAYOUT>(wire, wb + 1, W, D0)] = w1;
+        auto write = [&](auto stream) {
+            for (int e = threadIdx.x; e < kWires * (cpb / 2); e += kThreads) {
+                const int r = e / (cpb / 2);                   // tile wire row
+                const int c2 = part * cpb + 2 * (e % (cpb / 2));   // even column
+                const int gi = r / G::kWPG, p = r % G::kWPG;
+                const int fg = gi * G::kFPG + p / B;           // feature of this wire in the tile
+                const int64_t wb = wb0 + c2;
+                if (fg < skip || fg >= nf || wb >= W_cols)
+                    continue;
+                const int64_t wire = (int64_t)(f0 + gi * G::kFPG) * B + p;
+                const uint64_t w0 = otile[r * kOtRow + c2], w1 = otile[r * kOtRow + c2 + 1];
+                uint64_t *q = out + out_index<LAYOUT>(wire, wb, W, D0);
+                if (wb + 1 < W_cols && (LAYOUT == kLayoutSlab || ((uintptr_t)q % 16) == 0)) {
+                    const u32x4 v = u32x4{(uint32_t)w0, (uint32_t)(w0 >> 32), (uint32_t)w1,
+                                          (uint32_t)(w1 >> 32)};
+                    if constexpr (decltype(stream)::value)
+                        __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(q));
+                    else
+                        *reinterpret_cast<u32x4 *>(q) = v;
+                } else {
+                    q[0] = w0;
+                    if (wb + 1 < W_cols)
+                        out[out_index<LAYOUT>(wire, wb + 1, W, D0)] = w1;
+                }
             }
-        }
+        };
+        if (nt)
+            write(std::true_type{});
+        else
+            write(std::false_type{});
         __syncthreads();       // tile written before the next one reuses it
     }
 }
@@ -369,7 +374,8 @@ hipError_t launch_tile(const uint8_t *x, int64_t n, int32_t d, const uint8_t *th
     const int vec16 = (d % 16 == 0) && ((uintptr_t)x % 16 == 0) && G::kFT % 16 == 0;
     hipLaunchKernelGGL((k_encode_t<B, LAYOUT, KG, CS>), dim3((unsigned)blocks), dim3(kThreads), 0,
                        stream, x, n, d, th, out, W, W_cols, n_ftiles, (int32_t)tpb, n_tiles, n_tg,
-                       vec16, kind);
+                       vec16, kind,
+                       (int)streams_past_cache((int64_t)d * B * W_cols * 8));
     return hipGetLastError();
 }
 

@@ -167,7 +167,7 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void *base, uint32_t bytes)
 // record array holds (kJumpPadRecs).
 __global__ __launch_bounds__(kJumpThreads) void k_jump_layer(
     const uint64_t *__restrict__ in, int32_t w_in, const uint32_t *__restrict__ rec,
-    int32_t w_out, uint64_t *__restrict__ out, int32_t n_nblk, int32_t n_pairs)
+    int32_t w_out, uint64_t *__restrict__ out, int32_t n_nblk, int32_t n_pairs, int nt)
 {
     constexpr int kRow = kSlabWords * 8;          // bytes of one row segment
     int pair, nblk;
@@ -263,9 +263,14 @@ __global__ __launch_bounds__(kJumpThreads) void k_jump_layer(
     // the wave's outputs, one half-word a lane and node: nodes n0 .. n0 + cnt
     // are rows of the slab pair's output, 128 bytes apart
     char *o = ob + vout + (uint32_t)n0 * kRow;
-    for (int i = 0; i < cnt; ++i)
-        __builtin_nontemporal_store(s_out[wave][i][lane],
-                                    reinterpret_cast<uint32_t *>(o + (uint32_t)i * kRow));
+    if (nt) {
+        for (int i = 0; i < cnt; ++i)
+            __builtin_nontemporal_store(s_out[wave][i][lane],
+                                        reinterpret_cast<uint32_t *>(o + (uint32_t)i * kRow));
+    } else {
+        for (int i = 0; i < cnt; ++i)
+            *reinterpret_cast<uint32_t *>(o + (uint32_t)i * kRow) = s_out[wave][i][lane];
+    }
 }
 
 }  // namespace
@@ -309,7 +314,8 @@ hipError_t launch_jump_layer(const uint64_t *in, int32_t w_in, int64_t n_slabs,
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_jump_layer, dim3((unsigned)blocks), dim3(kJumpThreads), 0, stream, in,
-                       w_in, rec, w_out, out, n_nblk, (int32_t)n_pairs);
+                       w_in, rec, w_out, out, n_nblk, (int32_t)n_pairs,
+                       (int)streams_past_cache((int64_t)w_out * n_slabs * kSlabWords * 8));
     return hipGetLastError();
 }
 

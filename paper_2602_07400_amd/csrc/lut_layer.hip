@@ -42,11 +42,8 @@ constexpr int kThreads = 256;
 // The LPN lanes of a node split its S words (R = S / LPN words each, loaded
 // as 16-byte pieces); a block handles one slab and NB nodes, so a wave's
 // stores are contiguous.  The per-XCD working set of a slab is w_in * S * 8
-// bytes.  Output stores are non-temporal so the output stream does not evict
-// the input slab from L2.
-#ifndef BL_NT_STORE
-#define BL_NT_STORE 1
-#endif
+// bytes.  Output stores past the memory-side cache are non-temporal, so that the
+// output stream does not evict the input slab from L2.
 
 template <int K, int R>
 __device__ __forceinline__ void gather(const uint64_t *src, const int32_t *c, int64_t S,
@@ -103,13 +100,13 @@ __device__ __forceinline__ void gather_off(const char *slab_base, uint32_t lane_
     }
 }
 
-template <int R>
+template <int R, bool NT>
 __device__ __forceinline__ void store_out(const uint32_t (&o)[2 * R], uint64_t *q, bool ok)
 {
     if (ok) {
         if constexpr (R == 1) {
             const uint64_t v = (uint64_t)o[1] << 32 | o[0];
-            if (BL_NT_STORE)
+            if constexpr (NT)
                 __builtin_nontemporal_store(v, q);
             else
                 *q = v;
@@ -117,7 +114,7 @@ __device__ __forceinline__ void store_out(const uint32_t (&o)[2 * R], uint64_t *
 #pragma unroll
             for (int r = 0; r < R; r += 2) {
                 const u32x4 v = u32x4{o[2 * r], o[2 * r + 1], o[2 * r + 2], o[2 * r + 3]};
-                if (BL_NT_STORE)
+                if constexpr (NT)
                     __builtin_nontemporal_store(v, reinterpret_cast<u32x4_a8 *>(q) + r / 2);
                 else
                     reinterpret_cast<u32x4_a8 *>(q)[r / 2] = v;
@@ -126,13 +123,13 @@ __device__ __forceinline__ void store_out(const uint32_t (&o)[2 * R], uint64_t *
     }
 }
 
-template <int K, int R>
+template <int K, int R, bool NT>
 __device__ __forceinline__ void eval_store(uint64_t T, const uint32_t (&xv)[2 * R][K],
                                            uint64_t *q, bool ok)
 {
     uint32_t o[2 * R];
     eval_node<K, R>(T, xv, o);
-    store_out<R>(o, q, ok);
+    store_out<R, NT>(o, q, ok);
 }
 
 // Specialized layers (table specialization, see specialize.hip): the nodes of
@@ -261,7 +258,7 @@ constexpr int split_depth()
 // s_conn (KS = KP, or the layer's fan-in for a specialized block of fan-in
 // KP: the first KP slots give each node's output); KP = 0 is a constant node
 // (table bit 0).
-template <int KP, int KS, int R, int NPASS, int kPassNodes>
+template <int KP, int KS, int R, int NPASS, int kPassNodes, bool NT>
 __device__ __forceinline__ void split_passes(const uint64_t *src, const int32_t *s_conn,
                                              const uint64_t *s_tab, int lnode, int64_t S,
                                              uint64_t *dst)
@@ -300,24 +297,24 @@ __device__ __forceinline__ void split_passes(const uint64_t *src, const int32_t 
     }
 #pragma unroll
     for (int p = 0; p < NPASS; ++p)
-        store_out<R>(o[p], dst + (int64_t)(p * kPassNodes + lnode) * S, true);
+        store_out<R, NT>(o[p], dst + (int64_t)(p * kPassNodes + lnode) * S, true);
 }
 
 // split_passes at the block's fan-in kp (wave-uniform, 0 <= kp <= K).
-template <int KQ, int K, int R, int NPASS, int kPassNodes>
+template <int KQ, int K, int R, int NPASS, int kPassNodes, bool NT>
 __device__ __forceinline__ void split_passes_kp(int kp, const uint64_t *src,
                                                 const int32_t *s_conn, const uint64_t *s_tab,
                                                 int lnode, int64_t S, uint64_t *dst)
 {
     if (kp == KQ) {
-        split_passes<KQ, K, R, NPASS, kPassNodes>(src, s_conn, s_tab, lnode, S, dst);
+        split_passes<KQ, K, R, NPASS, kPassNodes, NT>(src, s_conn, s_tab, lnode, S, dst);
         return;
     }
     if constexpr (KQ < K)
-        split_passes_kp<KQ + 1, K, R, NPASS, kPassNodes>(kp, src, s_conn, s_tab, lnode, S, dst);
+        split_passes_kp<KQ + 1, K, R, NPASS, kPassNodes, NT>(kp, src, s_conn, s_tab, lnode, S, dst);
 }
 
-template <int K, int S, int LPN, int NB, bool SPEC>
+template <int K, int S, int LPN, int NB, bool SPEC, bool NT>
 __global__ __launch_bounds__(kThreads, BL_LUT_MINWAVES) void k_lut_slab(
     const uint64_t *__restrict__ in, int32_t w_in, const int32_t *__restrict__ conn,
     const uint64_t *__restrict__ tables, int32_t w_out, uint64_t *__restrict__ out,
@@ -362,12 +359,12 @@ __global__ __launch_bounds__(kThreads, BL_LUT_MINWAVES) void k_lut_slab(
                 const int kmin = __builtin_amdgcn_readfirstlane(s_kp[kPasses]);
                 const int kmax = __builtin_amdgcn_readfirstlane(s_kp[kPasses + 1]);
                 if (kmin == kmax) {
-                    split_passes_kp<0, K, R, kPasses, kPassNodes>(kmax, src, s_conn, s_tab, lnode,
+                    split_passes_kp<0, K, R, kPasses, kPassNodes, NT>(kmax, src, s_conn, s_tab, lnode,
                                                                   S, dst);
                     return;
                 }
             } else {
-                split_passes<K, K, R, kPasses, kPassNodes>(src, s_conn, s_tab, lnode, S, dst);
+                split_passes<K, K, R, kPasses, kPassNodes, NT>(src, s_conn, s_tab, lnode, S, dst);
                 return;
             }
         }
@@ -389,7 +386,7 @@ __global__ __launch_bounds__(kThreads, BL_LUT_MINWAVES) void k_lut_slab(
                 if (BL_PF_SETPRIO)
                     asm volatile("s_setprio 0" ::: "memory");
             }
-            eval_store<K, R>(s_tab[jl], xa, dst + (int64_t)jl * S, jl < nodes);
+            eval_store<K, R, NT>(s_tab[jl], xa, dst + (int64_t)jl * S, jl < nodes);
             if (pass + 1 < npass) {
                 if (pass + 2 < npass) {
                     if (BL_PF_SETPRIO)
@@ -398,7 +395,7 @@ __global__ __launch_bounds__(kThreads, BL_LUT_MINWAVES) void k_lut_slab(
                     if (BL_PF_SETPRIO)
                         asm volatile("s_setprio 0" ::: "memory");
                 }
-                eval_store<K, R>(s_tab[jl1], xb, dst + (int64_t)jl1 * S, jl1 < nodes);
+                eval_store<K, R, NT>(s_tab[jl1], xb, dst + (int64_t)jl1 * S, jl1 < nodes);
             }
         }
         return;
@@ -410,11 +407,11 @@ __global__ __launch_bounds__(kThreads, BL_LUT_MINWAVES) void k_lut_slab(
             const int kp = __builtin_amdgcn_readfirstlane(s_kp[pass]);
             uint32_t o[2 * R];
             spec_eval<0, K, R>(kp, src, &s_conn[jl * K], S, s_tab[jl], o);
-            store_out<R>(o, dst + (int64_t)jl * S, jl < nodes);
+            store_out<R, NT>(o, dst + (int64_t)jl * S, jl < nodes);
         } else {
             uint32_t xv[2 * R][K];
             gather<K, R>(src, &s_conn[jl * K], S, xv);
-            eval_store<K, R>(s_tab[jl], xv, dst + (int64_t)jl * S, jl < nodes);
+            eval_store<K, R, NT>(s_tab[jl], xv, dst + (int64_t)jl * S, jl < nodes);
         }
     }
 }
@@ -437,8 +434,8 @@ constexpr int slab_lanes()
     return K <= 4 ? 8 : kSlabLanes;
 }
 
-template <int K, int NB>
-hipError_t launch_slab_kn(const uint64_t *in, int32_t w_in, int64_t n_slabs,
+template <int K, int NB, bool NT>
+hipError_t launch_slab_nt(const uint64_t *in, int32_t w_in, int64_t n_slabs,
                           const int32_t *conn, const uint64_t *tables, int32_t w_out,
                           uint64_t *out, const uint8_t *fanin, hipStream_t stream)
 {
@@ -447,14 +444,25 @@ hipError_t launch_slab_kn(const uint64_t *in, int32_t w_in, int64_t n_slabs,
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     if (fanin)
-        hipLaunchKernelGGL((k_lut_slab<K, kSlabWords, slab_lanes<K>(), NB, true>),
+        hipLaunchKernelGGL((k_lut_slab<K, kSlabWords, slab_lanes<K>(), NB, true, NT>),
                            dim3((unsigned)blocks), dim3(kThreads), 0, stream, in, w_in, conn,
                            tables, w_out, out, n_nblk, (int32_t)n_slabs, fanin);
     else
-        hipLaunchKernelGGL((k_lut_slab<K, kSlabWords, slab_lanes<K>(), NB, false>),
+        hipLaunchKernelGGL((k_lut_slab<K, kSlabWords, slab_lanes<K>(), NB, false, NT>),
                            dim3((unsigned)blocks), dim3(kThreads), 0, stream, in, w_in, conn,
                            tables, w_out, out, n_nblk, (int32_t)n_slabs, fanin);
     return hipGetLastError();
+}
+
+template <int K, int NB>
+hipError_t launch_slab_kn(const uint64_t *in, int32_t w_in, int64_t n_slabs,
+                          const int32_t *conn, const uint64_t *tables, int32_t w_out,
+                          uint64_t *out, const uint8_t *fanin, bool nt, hipStream_t stream)
+{
+    return nt ? launch_slab_nt<K, NB, true>(in, w_in, n_slabs, conn, tables, w_out, out, fanin,
+                                            stream)
+              : launch_slab_nt<K, NB, false>(in, w_in, n_slabs, conn, tables, w_out, out, fanin,
+                                             stream);
 }
 
 template <int K>
@@ -462,11 +470,12 @@ hipError_t launch_slab_k(const uint64_t *in, int32_t w_in, int64_t n_slabs,
                          const int32_t *conn, const uint64_t *tables, int32_t w_out,
                          uint64_t *out, const uint8_t *fanin, hipStream_t stream)
 {
+    const bool nt = streams_past_cache((int64_t)w_out * n_slabs * kSlabWords * 8);
     const int64_t big = n_slabs * ((w_out + kSlabNB - 1) / kSlabNB);
     if (big < kSlabSmallBlocks)     // one pass per block
         return launch_slab_kn<K, kThreads / slab_lanes<K>()>(in, w_in, n_slabs, conn, tables,
-                                                             w_out, out, fanin, stream);
-    return launch_slab_kn<K, kSlabNB>(in, w_in, n_slabs, conn, tables, w_out, out, fanin,
+                                                             w_out, out, fanin, nt, stream);
+    return launch_slab_kn<K, kSlabNB>(in, w_in, n_slabs, conn, tables, w_out, out, fanin, nt,
                                       stream);
 }
 
@@ -867,7 +876,7 @@ constexpr int kRowsLPN = 8;
 constexpr int kRowsNB = 128;
 constexpr int64_t kRowsSmallBlocks = 4096;
 
-template <int K, int LPN, int NB>
+template <int K, int LPN, int NB, bool NT>
 __global__ __launch_bounds__(kThreads) void k_lut_rows(
     const uint64_t *__restrict__ in, int64_t W, const int32_t *__restrict__ conn,
     const uint64_t *__restrict__ tables, int32_t w_out, uint64_t *__restrict__ out,
@@ -900,7 +909,7 @@ __global__ __launch_bounds__(kThreads) void k_lut_rows(
     if ((int64_t)(win + 1) * kSlabWords <= W) {
         if constexpr (slab_prefetch<K>() && kPasses >= 2) {
             if (nodes == NB) {
-                split_passes<K, K, R, kPasses, kPassNodes>(src, s_conn, s_tab, lnode, W, dst);
+                split_passes<K, K, R, kPasses, kPassNodes, NT>(src, s_conn, s_tab, lnode, W, dst);
                 return;
             }
         }
@@ -909,7 +918,7 @@ __global__ __launch_bounds__(kThreads) void k_lut_rows(
             const int jl = pass * kPassNodes + lnode;
             uint32_t xv[2 * R][K];
             gather<K, R>(src, &s_conn[jl * K], W, xv);
-            eval_store<K, R>(s_tab[jl], xv, dst + jl * W, jl < nodes);
+            eval_store<K, R, NT>(s_tab[jl], xv, dst + jl * W, jl < nodes);
         }
         return;
     }
@@ -923,7 +932,7 @@ __global__ __launch_bounds__(kThreads) void k_lut_rows(
             uint32_t xv[2][K], o[2];
             gather<K, 1>(in + min(wb0 + r, W - 1), &s_conn[jl * K], W, xv);
             eval_node<K, 1>(s_tab[jl], xv, o);
-            store_out<1>(o, dst + jl * W + r, jl < nodes && wb0 + r < W);
+            store_out<1, NT>(o, dst + jl * W + r, jl < nodes && wb0 + r < W);
         }
     }
 }
@@ -938,9 +947,14 @@ hipError_t launch_rows_kn(const uint64_t *in, int64_t W, const int32_t *conn,
     const int64_t blocks = dealt_blocks(n_win, n_nblk);
     if (blocks > 0x7fffffff || n_win > 0x7fffffff)
         return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((k_lut_rows<K, kRowsLPN, NB>), dim3((unsigned)blocks),
-                       dim3(kThreads), 0, stream, in, W, conn, tables, w_out, out, n_nblk,
-                       (int32_t)n_win);
+    if (streams_past_cache((int64_t)w_out * W * 8))
+        hipLaunchKernelGGL((k_lut_rows<K, kRowsLPN, NB, true>), dim3((unsigned)blocks),
+                           dim3(kThreads), 0, stream, in, W, conn, tables, w_out, out, n_nblk,
+                           (int32_t)n_win);
+    else
+        hipLaunchKernelGGL((k_lut_rows<K, kRowsLPN, NB, false>), dim3((unsigned)blocks),
+                           dim3(kThreads), 0, stream, in, W, conn, tables, w_out, out, n_nblk,
+                           (int32_t)n_win);
     return hipGetLastError();
 }
 
