@@ -407,6 +407,7 @@ int forward_columns(const bitlogic_network *net, const ForwardPlan &fp, const ui
         for (int32_t l = 0; l < L; ++l) {
             cn.conn[l] = layers[l].conn;
             cn.tables[l] = layers[l].tables;
+            cn.fanin[l] = net->pass_fanin ? net->pass_fanin[l] : nullptr;
         }
         e = bl::launch_column_network(x, n, net->n_features, net->thresholds, net->n_bits, kind,
                                       cn, c, !dsp && !scores ? nullptr : counts,
@@ -426,7 +427,8 @@ int forward_columns(const bitlogic_network *net, const ForwardPlan &fp, const ui
     int32_t w_in = net->n_features * net->n_bits;
     for (int32_t l = 0; l < L - 1; ++l) {
         e = bl::launch_column_layer(cur, w_in, (int32_t)fp.W, layers[l].conn, layers[l].tables,
-                                    layers[l].w_out, layers[l].k, act[l & 1], s);
+                                    layers[l].w_out, layers[l].k, act[l & 1],
+                                    net->pass_fanin ? net->pass_fanin[l] : nullptr, s);
         if (e == hipSuccess)
             e = mark(2 + l);
         if (e != hipSuccess)
@@ -436,7 +438,8 @@ int forward_columns(const bitlogic_network *net, const ForwardPlan &fp, const ui
     }
     e = bl::launch_column_head(cur, w_in, layers[L - 1].conn, layers[L - 1].tables,
                                layers[L - 1].w_out, layers[L - 1].k, c, n, fp.cols, counts,
-                               dsp ? nullptr : argmax, s);
+                               dsp ? nullptr : argmax,
+                               net->pass_fanin ? net->pass_fanin[L - 1] : nullptr, s);
     if (e == hipSuccess)
         e = mark(L + 1);
     if (e == hipSuccess && dsp)

@@ -197,6 +197,7 @@ hipError_t launch_grouped_dsp(const int32_t *counts, int64_t n, int32_t c,
                               hipStream_t stream);
 
 // Small batches by 64-sample columns (columns.hip): packed tensors [W][rows].
+// fanin: NULL, or a specialized layer's fan-in per kSpecPass nodes (device).
 // plan_column_head: the classes of one head block (cpb, splits blocks a
 // column), whether it stages the column's rows in LDS, its LDS bytes, and
 // whether the column kernels can run it.
@@ -216,6 +217,7 @@ struct ColumnNetwork {
     int32_t w[kColumnMaxLayers], k[kColumnMaxLayers];
     const int32_t *conn[kColumnMaxLayers];
     const uint64_t *tables[kColumnMaxLayers];
+    const uint8_t *fanin[kColumnMaxLayers];      // of specialized layers, else NULL
     size_t lds;
 };
 ColumnNetwork plan_column_network(int32_t d, int32_t b, const int32_t *w, const int32_t *k,
@@ -227,13 +229,13 @@ hipError_t launch_column_encode(const uint8_t *x, int64_t n, int32_t d, const ui
                                 int32_t b, uint64_t *out, int kind, hipStream_t stream);
 hipError_t launch_column_layer(const uint64_t *in, int32_t w_in, int32_t W, const int32_t *conn,
                                const uint64_t *tables, int32_t w_out, int32_t k, uint64_t *out,
-                               hipStream_t stream);
+                               const uint8_t *fanin, hipStream_t stream);
 // Last layer and GroupSum: counts int32 [n][c] (may be NULL if splits == 1) and
 // argmax (may be NULL).
 hipError_t launch_column_head(const uint64_t *in, int32_t w_in, const int32_t *conn,
                               const uint64_t *tables, int32_t w_out, int32_t k, int32_t c,
                               int64_t n, const ColumnHeadPlan &hp, int32_t *counts,
-                              int32_t *argmax, hipStream_t stream);
+                              int32_t *argmax, const uint8_t *fanin, hipStream_t stream);
 
 // Peak probes (probes.hip): kProbeThreads = 256 lanes a block.
 hipError_t launch_probe_valu(uint32_t *out, int32_t blocks, int32_t iters, uint32_t seed,

@@ -31,6 +31,8 @@
 // 19.7 -> 13.0 us; 784 -> 1000 -> 1000, fan-in 6, at 4096 samples 18.8 -> 13.0;
 // 784 x 7 -> 8000 -> 8000, fan-in 6, at 1024 31.9 -> 17.8; 9216 -> 32000 ->
 // 32000, fan-in 6, at 64 78 -> 25 (37 with the slab's blocks on all XCDs).
+#include <type_traits>
+
 #include "bl_device.h"
 #include "encode_row.h"
 
@@ -43,6 +45,21 @@ constexpr int kThreads = 256;
 constexpr int kHeadThreads = 1024;
 constexpr int kHeadWaves = kHeadThreads / kWave;
 constexpr int kCntStride = kWave + 1;         // LDS words per class of counts
+
+// A node of a layer with a fan-in array, whose output its first kp slots give
+// whatever the others hold: the others read wire 0 and the table, repeated over
+// them, ignores them, so that nodes of all fan-ins run as nodes of K inputs.
+// kp >= K changes nothing.
+template <int K>
+__device__ __forceinline__ void keep_slots(int kp, int32_t *idx, uint64_t &T)
+{
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        const uint64_t low = (1ull << (1 << i)) - 1;
+        T = i < kp ? T : (T & low) | T << (1 << i);
+        idx[i] = i < kp ? idx[i] : 0;
+    }
+}
 
 // One wave's group of features of one column: their pixels (a lane a sample)
 // and, in lane k < kS, the thresholds of slot k.
@@ -139,7 +156,7 @@ template <int K, int C>
 __global__ __launch_bounds__(kThreads) void k_col_layer(
     const uint64_t *__restrict__ in, int32_t w_in, const int32_t *__restrict__ conn,
     const uint64_t *__restrict__ tables, int32_t w_out, uint64_t *__restrict__ out, int32_t W,
-    int32_t n_cg)
+    int32_t n_cg, const uint8_t *__restrict__ fanin)
 {
     // column groups vary fastest, so that blocks of one group tend to share
     // an XCD and its L2
@@ -150,7 +167,9 @@ __global__ __launch_bounds__(kThreads) void k_col_layer(
 #pragma unroll
     for (int i = 0; i < K; ++i)
         idx[i] = conn[(int64_t)jc * K + i];
-    const uint64_t T = tables[jc];
+    uint64_t T = tables[jc];
+    if (fanin)
+        keep_slots<K>(fanin[jc / kSpecPass], idx, T);
     uint32_t xv[2 * C][K], o[2 * C];
 #pragma unroll
     for (int r = 0; r < C; ++r) {
@@ -237,7 +256,8 @@ template <int K, bool STAGED>
 __global__ __launch_bounds__(kHeadThreads) void k_col_head(
     const uint64_t *__restrict__ in, int32_t w_in, const int32_t *__restrict__ conn,
     const uint64_t *__restrict__ tables, int32_t g, int32_t c, int32_t cpb, int64_t n,
-    int32_t *__restrict__ counts, int32_t *__restrict__ argmax)
+    int32_t *__restrict__ counts, int32_t *__restrict__ argmax,
+    const uint8_t *__restrict__ fanin)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint64_t *s_in = reinterpret_cast<uint64_t *>(smem);
@@ -254,12 +274,15 @@ __global__ __launch_bounds__(kHeadThreads) void k_col_head(
     // the wave's first nodes, requested before the rows are staged
     int32_t idx[K];
     uint64_t T = 0;
+    int kp = K;
     auto fetch = [&](int base) {
         const int j = min(base + lane, n1 - 1);
 #pragma unroll
         for (int i = 0; i < K; ++i)
             idx[i] = conn[(int64_t)j * K + i];
         T = tables[j];
+        if (fanin)
+            kp = fanin[j / kSpecPass];
     };
     int base = n0 + wave * kWave;
     if (base < n1)
@@ -279,6 +302,8 @@ __global__ __launch_bounds__(kHeadThreads) void k_col_head(
 
     const dev::Transpose tr = transpose_consts(lane);
     while (base < n1) {
+        if (fanin)
+            keep_slots<K>(kp, idx, T);
         uint32_t xv[2][K], o[2];
 #pragma unroll
         for (int i = 0; i < K; ++i) {
@@ -316,8 +341,9 @@ __device__ __forceinline__ void eval_lds(const uint64_t *s_in, const int32_t (&i
 
 // The whole network of one column in one block: wires, hidden layers and counts
 // in LDS (two buffers of rows_a and rows_b words, used in turn, then the counts
-// and argmax partials).
-template <int B>
+// and argmax partials).  SPEC: some layer has a fan-in array (tested per layer
+// in the plain kernel it cost 0.2 of the 9.9 us of 784 -> 1000 -> 1000).
+template <int B, bool SPEC>
 __global__ __launch_bounds__(kHeadThreads) void k_col_network(
     const uint8_t *__restrict__ x, int64_t n, int32_t d, const uint8_t *__restrict__ th, int kind,
     int32_t n_ftiles, ColumnNetwork net, int32_t rows_a, int32_t rows_b, int32_t c,
@@ -336,6 +362,7 @@ __global__ __launch_bounds__(kHeadThreads) void k_col_network(
     // the next nodes' connections and tables, always one task ahead
     int32_t idx[6];
     uint64_t T = 0;
+    int kp = 6;
     auto fetch = [&](int l, int base) {
         const int k = net.k[l], j = min(base + lane, net.w[l] - 1);
         const int32_t *src = net.conn[l] + (int64_t)j * k;
@@ -349,6 +376,8 @@ __global__ __launch_bounds__(kHeadThreads) void k_col_network(
         default: __builtin_memcpy(idx, src, 24); break;
         }
         T = net.tables[l][j];
+        if (SPEC && net.fanin[l])
+            kp = net.fanin[l][j / kSpecPass];
     };
     if (wave < n_ftiles) {
         ColGroup<B> cur, next;
@@ -386,7 +415,9 @@ __global__ __launch_bounds__(kHeadThreads) void k_col_network(
 #pragma unroll
             for (int i = 0; i < 6; ++i)
                 at[i] = idx[i];
-            const uint64_t Tc = T;
+            uint64_t Tc = T;
+            if (SPEC && net.fanin[l])
+                keep_slots<6>(kp, at, Tc);
             if (base + kHeadThreads < w)
                 fetch(l, base + kHeadThreads);
             else if (!last)
@@ -448,55 +479,59 @@ hipError_t launch_network_b(const uint8_t *x, int64_t n, int32_t d, const uint8_
                             hipStream_t stream)
 {
     constexpr int F = EncGeom<B, 1>::kFPG;
-    hipLaunchKernelGGL(k_col_network<B>, dim3((unsigned)((n + 63) / 64)), dim3(kHeadThreads),
-                       net.lds, stream, x, n, d, th, kind, (d + F - 1) / F, net, net.rows_a,
-                       net.rows_b, c, counts, argmax);
+    bool spec = false;
+    for (int32_t l = 0; l < net.n_layers; ++l)
+        spec = spec || net.fanin[l];
+    const auto kernel = spec ? k_col_network<B, true> : k_col_network<B, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 63) / 64)), dim3(kHeadThreads), net.lds,
+                       stream, x, n, d, th, kind, (d + F - 1) / F, net, net.rows_a, net.rows_b, c,
+                       counts, argmax);
     return hipGetLastError();
 }
 
 template <int K, int C>
 hipError_t launch_layer_kc(const uint64_t *in, int32_t w_in, const int32_t *conn,
                            const uint64_t *tables, int32_t w_out, uint64_t *out, int32_t W,
-                           hipStream_t stream)
+                           const uint8_t *fanin, hipStream_t stream)
 {
     const int32_t n_cg = (W + C - 1) / C;
     const int64_t blocks = (int64_t)n_cg * ((w_out + kThreads - 1) / kThreads);
     if (blocks > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((k_col_layer<K, C>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, in,
-                       w_in, conn, tables, w_out, out, W, n_cg);
+                       w_in, conn, tables, w_out, out, W, n_cg, fanin);
     return hipGetLastError();
 }
 
 template <int K>
 hipError_t launch_layer_k(const uint64_t *in, int32_t w_in, const int32_t *conn,
                           const uint64_t *tables, int32_t w_out, uint64_t *out, int32_t W,
-                          hipStream_t stream)
+                          const uint8_t *fanin, hipStream_t stream)
 {
     // a lane serves 4 or 2 columns of its node once that still leaves a wave
     // per SIMD: the table's masks are then extracted once for all of them
     const int64_t waves = (int64_t)W * ((w_out + kWave - 1) / kWave);
     if (waves >= 4 * 2048 && W >= 4)
-        return launch_layer_kc<K, 4>(in, w_in, conn, tables, w_out, out, W, stream);
+        return launch_layer_kc<K, 4>(in, w_in, conn, tables, w_out, out, W, fanin, stream);
     if (waves >= 2 * 2048 && W >= 2)
-        return launch_layer_kc<K, 2>(in, w_in, conn, tables, w_out, out, W, stream);
-    return launch_layer_kc<K, 1>(in, w_in, conn, tables, w_out, out, W, stream);
+        return launch_layer_kc<K, 2>(in, w_in, conn, tables, w_out, out, W, fanin, stream);
+    return launch_layer_kc<K, 1>(in, w_in, conn, tables, w_out, out, W, fanin, stream);
 }
 
 template <int K>
 hipError_t launch_head_k(const uint64_t *in, int32_t w_in, const int32_t *conn,
                          const uint64_t *tables, int32_t g, int32_t c, int64_t n,
                          const ColumnHeadPlan &hp, int32_t *counts, int32_t *argmax,
-                         hipStream_t stream)
+                         const uint8_t *fanin, hipStream_t stream)
 {
     const dim3 grid((unsigned)((n + 63) / 64), (unsigned)hp.splits);
     int32_t *am = hp.splits == 1 ? argmax : nullptr;
     if (hp.staged)
         hipLaunchKernelGGL((k_col_head<K, true>), grid, dim3(kHeadThreads), hp.lds, stream, in,
-                           w_in, conn, tables, g, c, hp.cpb, n, counts, am);
+                           w_in, conn, tables, g, c, hp.cpb, n, counts, am, fanin);
     else
         hipLaunchKernelGGL((k_col_head<K, false>), grid, dim3(kHeadThreads), hp.lds, stream, in,
-                           w_in, conn, tables, g, c, hp.cpb, n, counts, am);
+                           w_in, conn, tables, g, c, hp.cpb, n, counts, am, fanin);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || hp.splits == 1 || !argmax)
         return e;
@@ -603,15 +638,15 @@ hipError_t launch_column_network(const uint8_t *x, int64_t n, int32_t d, const u
 
 hipError_t launch_column_layer(const uint64_t *in, int32_t w_in, int32_t W, const int32_t *conn,
                                const uint64_t *tables, int32_t w_out, int32_t k, uint64_t *out,
-                               hipStream_t stream)
+                               const uint8_t *fanin, hipStream_t stream)
 {
     switch (k) {
-    case 1: return launch_layer_k<1>(in, w_in, conn, tables, w_out, out, W, stream);
-    case 2: return launch_layer_k<2>(in, w_in, conn, tables, w_out, out, W, stream);
-    case 3: return launch_layer_k<3>(in, w_in, conn, tables, w_out, out, W, stream);
-    case 4: return launch_layer_k<4>(in, w_in, conn, tables, w_out, out, W, stream);
-    case 5: return launch_layer_k<5>(in, w_in, conn, tables, w_out, out, W, stream);
-    case 6: return launch_layer_k<6>(in, w_in, conn, tables, w_out, out, W, stream);
+    case 1: return launch_layer_k<1>(in, w_in, conn, tables, w_out, out, W, fanin, stream);
+    case 2: return launch_layer_k<2>(in, w_in, conn, tables, w_out, out, W, fanin, stream);
+    case 3: return launch_layer_k<3>(in, w_in, conn, tables, w_out, out, W, fanin, stream);
+    case 4: return launch_layer_k<4>(in, w_in, conn, tables, w_out, out, W, fanin, stream);
+    case 5: return launch_layer_k<5>(in, w_in, conn, tables, w_out, out, W, fanin, stream);
+    case 6: return launch_layer_k<6>(in, w_in, conn, tables, w_out, out, W, fanin, stream);
     default: return hipErrorInvalidValue;
     }
 }
@@ -619,16 +654,20 @@ hipError_t launch_column_layer(const uint64_t *in, int32_t w_in, int32_t W, cons
 hipError_t launch_column_head(const uint64_t *in, int32_t w_in, const int32_t *conn,
                               const uint64_t *tables, int32_t w_out, int32_t k, int32_t c,
                               int64_t n, const ColumnHeadPlan &hp, int32_t *counts,
-                              int32_t *argmax, hipStream_t stream)
+                              int32_t *argmax, const uint8_t *fanin, hipStream_t stream)
 {
     const int32_t g = w_out / c;
+    auto run = [&](auto kc) {
+        return launch_head_k<decltype(kc)::value>(in, w_in, conn, tables, g, c, n, hp, counts,
+                                                  argmax, fanin, stream);
+    };
     switch (k) {
-    case 1: return launch_head_k<1>(in, w_in, conn, tables, g, c, n, hp, counts, argmax, stream);
-    case 2: return launch_head_k<2>(in, w_in, conn, tables, g, c, n, hp, counts, argmax, stream);
-    case 3: return launch_head_k<3>(in, w_in, conn, tables, g, c, n, hp, counts, argmax, stream);
-    case 4: return launch_head_k<4>(in, w_in, conn, tables, g, c, n, hp, counts, argmax, stream);
-    case 5: return launch_head_k<5>(in, w_in, conn, tables, g, c, n, hp, counts, argmax, stream);
-    case 6: return launch_head_k<6>(in, w_in, conn, tables, g, c, n, hp, counts, argmax, stream);
+    case 1: return run(std::integral_constant<int, 1>{});
+    case 2: return run(std::integral_constant<int, 2>{});
+    case 3: return run(std::integral_constant<int, 3>{});
+    case 4: return run(std::integral_constant<int, 4>{});
+    case 5: return run(std::integral_constant<int, 5>{});
+    case 6: return run(std::integral_constant<int, 6>{});
     default: return hipErrorInvalidValue;
     }
 }

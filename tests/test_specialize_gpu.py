@@ -170,3 +170,49 @@ def test_specialized_large_batch_block_modes():
     m = _check(x, th, layers, 10, 0.0)
     assert [int(conn.shape[1]) for conn, _ in m.layers] == [4, 2, 1, 3]
     assert m.plan(n)["fused_head"]
+
+
+@pytest.mark.parametrize("n,widths,ks,fanins", [
+    (130, (500, 300), (4, 6), (2, 3)),            # a column's network in one block
+    (130, (300, 320, 200), (6, 5, 3), (0, None, 9)),
+    (130, (2500, 4000), (5, 6), (1, 4)),          # column stages, rows in LDS
+    (70, (21001, 900), (3, 2), (2, 1)),           # and gathered
+    (64 * 40, (9001, 100), (4, 4), (3, 2)),       # two columns a lane
+    (64 * 60 - 1, (9001, 100), (4, 6), (1, 5)),   # four
+    (64 * 16 * 40, (3000, 2560), (6, 4), (3, 2)),   # slab kernels
+])
+def test_fan_ins_given_by_hand(n, widths, ks, fanins):
+    # fan-in arrays that bitlogic_specialize_network did not make: a layer's
+    # nodes read their first fan-in slots whatever the slots and table entries
+    # past them hold; None: no array; 0: the constant of table bit 0; above k: k
+    rng = np.random.default_rng(n + widths[0])
+    d, b, c = 400, 3, 10
+    x = rng.integers(0, 256, size=(n, d), dtype=np.uint8)
+    th = rng.integers(0, 256, size=(d, b), dtype=np.uint8)
+    layers, read, w_in = [], [], d * b
+    for w, k, f in zip(widths, ks, fanins):
+        conn = np.stack([rng.choice(w_in, size=k, replace=False) for _ in range(w)])
+        conn = conn.astype(np.int32)
+        tab = rng.integers(0, 1 << 63, size=w, dtype=np.uint64) << np.uint64(1)
+        tab |= rng.integers(0, 2, size=w).astype(np.uint64)
+        layers.append((conn, tab))
+        f = k if f is None else min(f, k)
+        # the oracle takes 1 and more inputs: a constant as a node of one input
+        read.append((conn, tab) if f == k else
+                    (np.ascontiguousarray(conn[:, :max(f, 1)]),
+                     tab if f else (tab & np.uint64(1)) * np.uint64(3)))
+        w_in = w
+    m = bl.BitlogicModel.from_numpy(th, layers, c, device=DEV)
+    m.pass_fanin = [None if f is None else
+                    torch.full(((w + 31) // 32,), f, dtype=torch.uint8, device=DEV)
+                    for w, f in zip(widths, fanins)]
+    xd = torch.from_numpy(x).to(DEV)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(layers) + 3)]
+    for e in ev:
+        e.record()
+    want, best = oracle.forward(x, th, read, c)
+    print(f"[spec-hand] n={n} widths={widths} k={ks} fan-ins={fanins}", flush=True)
+    for events in (None, ev):                     # untimed and stage by stage
+        s, p = m.forward(xd, events=events)
+        assert np.array_equal(s.cpu().numpy(), want), events
+        assert np.array_equal(p.cpu().numpy(), best), events
