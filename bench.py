@@ -21,8 +21,8 @@ Prints ONE JSON line.  Besides the driver's fields it carries
                 (integer VALU rate, HBM copy rate) with the dominant kernel's
                 fraction of them.
 
-Algorithmic work follows the path the library takes (bitlogic_forward_plan):
-when the last LUT layer is fused with the GroupSum head its output bits are
+Algorithmic work follows the path the library takes (bitlogic_forward_plan and
+bitlogic_network_path): when the last LUT layer is fused with the GroupSum head its output bits are
 never stored, so that stage's compulsory bytes are its input only and the
 head's counting is charged to it; a layer that the node-per-wave kernel runs
 (table-selected 3-input leaves, plan "jump_layers") is charged its 15
@@ -92,13 +92,20 @@ def parse():
     return ap.parse_args()
 
 
-def algorithmic(cfg, n, fused_head, binary_bits=0, fanin_hist=None, jump_layers=()):
+def algorithmic(cfg, n, fused_head, binary_bits=0, fanin_hist=None, jump_layers=(),
+                path="slab", dsp=False):
     """Compulsory bytes and algorithmic 32-bit lane-ops per stage of one forward.
     fanin_hist: per layer, None or the node count per effective fan-in 0..6 of
     a specialized layer (its multiplexers: 2^k' - 1 per node).
     jump_layers: layers the node-per-wave kernel evaluates with table-selected
     3-input leaves: 8 leaves + 7 multiplexers = 15 lane-ops per node and 32
-    samples instead of 2^k - 1, which leaves such a layer bound by its bytes."""
+    samples instead of 2^k - 1, which leaves such a layer bound by its bytes.
+    path: "columns" counts and takes the argmax in the last layer's kernel (a
+    quantized head, dsp, then reads the counts), "block" is one stage, which
+    reads the pixels and writes the outputs."""
+    fused_head = fused_head or path != "slab"
+    if path != "slab":
+        jump_layers = ()
     W = (n + 63) // 64
     D0 = cfg.d * (binary_bits or cfg.b)
     st = {"encode": {"bytes": n * cfg.d + D0 * W * 8, "ops": n * D0}}
@@ -121,6 +128,15 @@ def algorithmic(cfg, n, fused_head, binary_bits=0, fanin_hist=None, jump_layers=
         st["head"] = {"bytes": out_bytes, "ops": n * cfg.n_classes}
     else:
         st["head"] = {"bytes": w_in * W * 8 + out_bytes, "ops": n * w_in // 32}
+    if path == "block":
+        st = {"forward": {"bytes": n * cfg.d + out_bytes,
+                          "ops": sum(v["ops"] for v in st.values())}}
+    elif path == "columns":
+        last = st[f"layer{L}"]
+        last["bytes"] += 4 * n * cfg.n_classes if dsp else out_bytes
+        last["ops"] += st["head"]["ops"]
+        st["head"] = ({"bytes": 4 * n * cfg.n_classes + out_bytes, "ops": n * cfg.n_classes}
+                      if dsp else {"bytes": 0, "ops": 0})
     for v in st.values():
         t_mem = v["bytes"] / (PEAK_HBM_GBS * 1e9)
         t_alu = v["ops"] / (PEAK_VALU_TOPS * 1e12)
@@ -231,6 +247,12 @@ STAGE_KERNELS = {"encode": "k_encode_t / k_encode_ballot (encoder + bit-pack)",
                  "layer_fused": "k_lut_slab_head (last LUT layer fused with GroupSum counting)",
                  "head_fused": "k_head_finish (counts -> scores, argmax)",
                  "head": "k_head_planes + k_head_finish (GroupSum head, argmax)"}
+# the same of a batch that runs by 64-sample columns
+COLUMN_KERNELS = {"encode": "k_col_encode (encoder + bit-pack, a wave a column)",
+                  "layer": "k_col_layer (LUT layer, a lane a node)",
+                  "layer_last": "k_col_head (last LUT layer, counts and argmax of a column)",
+                  "head": "k_grouped_dsp (quantized head on the counts)",
+                  "forward": "k_col_network (a column's whole network in one block)"}
 
 
 def main():
@@ -312,18 +334,30 @@ def main():
     # ---- per-kernel times: the same forward with HIP events recorded by the
     # library at its stage boundaries, on the stream its kernels run on
     layer_names = [f"layer{l + 1}" for l in range(len(cfg.widths))]
-    names = ["encode"] + layer_names + ["head"]
+    path = model.path(n)
+    # a forward that is one kernel is one stage: asked for stage events, the
+    # library would run other kernels
+    if path == "block":
+        layer_names, names = [], ["forward"]
+    else:
+        names = ["encode"] + layer_names + ["head"]
     ksteps = args.stage_steps or args.steps
     sums = np.zeros(len(names))
     for it in range(ksteps + 2):
         ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(names) + 1)]
         for e in ev:
             e.record(stream)          # creates the HIP event handles
-        step(ev)
+        if path == "block":
+            ev[0].record(stream)
+            step()
+            ev[1].record(stream)
+        else:
+            step(ev)
         torch.cuda.synchronize()
         if it >= 2:                   # two untimed passes first
             sums += [ev[i].elapsed_time(ev[i + 1]) for i in range(len(names))]
-    stage_ms = dict(zip(names, (sums / ksteps).tolist()))
+    # a stage without a kernel (the GroupSum head of a batch run by columns) may read 0
+    stage_ms = dict(zip(names, np.maximum(sums / ksteps, 1e-6).tolist()))
     plan = model.plan(n)
 
     # ---- board power and engine clocks under a sustained load of the forward
@@ -470,8 +504,9 @@ def main():
                   "frac_of_hbm_peak": round(n * cfg.d / (fit_ms * 1e-3) / 1e9 / PEAK_HBM_GBS, 4)}
 
     fused = plan["fused_head"]
-    jump = plan.get("jump_layers", [])
-    alg = algorithmic(cfg, n, fused, binary_bits, model.fanin_histogram, jump)
+    jump = plan.get("jump_layers", []) if path == "slab" else []
+    alg = algorithmic(cfg, n, fused, binary_bits, model.fanin_histogram, jump, path,
+                      dsp_w is not None)
     roof_sum = sum(v["roof_ms"] for v in alg.values())
     # dominant kernel: the stage with the longest launch
     dom = max(names, key=lambda k: stage_ms[k])
@@ -482,7 +517,12 @@ def main():
     else:
         achieved = a["bytes"] / (stage_ms[dom] * 1e-3) / 1e9
         peak, unit, per = PEAK_HBM_GBS, "GB/s", f"{a['bytes']} bytes"
-    if dom == "encode":
+    if path != "slab":
+        kname = COLUMN_KERNELS["layer_last" if [dom] == layer_names[-1:] else
+                               "layer" if dom in layer_names else dom]
+        if path == "block" and dsp_w is not None:
+            kname += " + " + COLUMN_KERNELS["head"]
+    elif dom == "encode":
         kname = STAGE_KERNELS["encode"]
     elif dom == "head":
         kname = STAGE_KERNELS["head_fused" if fused else "head"]
@@ -511,7 +551,8 @@ def main():
         "forward_roofline_ms": round(roof_sum, 4),
         "forward_roofline_frac": round(roof_sum / ms_per_step, 4),
         "staged_sum_ms": round(sum(stage_ms.values()), 4),
-        "fused_head": fused,
+        "path": path,
+        "fused_head": fused if path == "slab" else None,
         "jump_layers": [layer_names[l] for l in jump],
         "specialized": bool(args.specialize),
         "fanin_histogram": ([None if h is None else [int(v) for v in h]

@@ -156,7 +156,7 @@ size_t bitlogic_forward_workspace_bytes(int64_t n_samples, int32_t n_features,
  * call, nothing enqueued).  It describes the slab kernels; small batches (of
  * networks of two and more layers and up to 8 wires a feature, without an
  * environment switch set) run by 64-sample columns in the same workspace, with
- * the same results.  Fills *info and returns BITLOGIC_OK, or returns
+ * the same results (bitlogic_network_path says which).  Fills *info and returns BITLOGIC_OK, or returns
  * the status bitlogic_forward would return for these sizes and descriptors
  * (info untouched).  Device pointers in `layers` are not dereferenced. */
 typedef struct bitlogic_forward_info {
@@ -371,6 +371,19 @@ size_t bitlogic_network_workspace_bytes(const bitlogic_network *net, int64_t n_s
 int bitlogic_network_plan(const bitlogic_network *net, int64_t n_samples,
                           bitlogic_forward_info *info);
 
+/* Which kernels bitlogic_network_forward runs n_samples on (host only, no HIP
+ * call, nothing enqueued), under the environment switches set at the call:
+ *   BITLOGIC_PATH_SLAB     the slab kernels that bitlogic_network_plan describes
+ *   BITLOGIC_PATH_COLUMNS  by 64-sample columns: encoder, layers, and the last
+ *                          layer with the GroupSum head (the quantized head
+ *                          follows as a kernel of its own)
+ *   BITLOGIC_PATH_BLOCK    by columns, a column's whole network in one block and
+ *                          kernel (with stage events: as BITLOGIC_PATH_COLUMNS)
+ * Fills *path and returns BITLOGIC_OK, or the status bitlogic_network_plan
+ * returns (path untouched).  The results do not depend on the path. */
+enum { BITLOGIC_PATH_SLAB = 0, BITLOGIC_PATH_COLUMNS = 1, BITLOGIC_PATH_BLOCK = 2 };
+int bitlogic_network_path(const bitlogic_network *net, int64_t n_samples, int32_t *path);
+
 /* The forward of a network descriptor: out [n_samples][c] int32 receives the
  * GroupSum scores or, with the quantized head, its logits; argmax [n_samples]
  * the lowest class holding the largest value (either may be NULL, not both).
@@ -508,8 +521,8 @@ const char *bitlogic_last_error(void);
  * fused_network member (the whole-network kernel was removed), and the
  * instruction-rate and gather probes; 0.7.0 bitlogic_forward_info.jump_layers
  * and the node-per-wave layer kernel, whose per-node records enlarge the
- * forward workspace of networks that use it). */
-#define BITLOGIC_VERSION 700
+ * forward workspace of networks that use it; 0.8.0 bitlogic_network_path). */
+#define BITLOGIC_VERSION 800
 int bitlogic_version(void);
 
 #ifdef __cplusplus

@@ -66,6 +66,7 @@ class _Network(ctypes.Structure):
                 ("head_weights", ctypes.c_void_p), ("pass_fanin", ctypes.c_void_p)]
 
 
+_PATHS = ("slab", "columns", "block")      # BITLOGIC_PATH_*
 MAX_FANIN = 6
 SPECIALIZE_PASS = 32          # nodes per entry of a specialized layer's fan-in array
 
@@ -98,6 +99,7 @@ def load_library():
         "bitlogic_fit_quantile_thresholds": ([P, i64, i32, i32, i32, P, P, sz, P], ctypes.c_int),
         "bitlogic_network_workspace_bytes": ([P, i64], sz),
         "bitlogic_network_plan": ([P, i64, P], ctypes.c_int),
+        "bitlogic_network_path": ([P, i64, P], ctypes.c_int),
         "bitlogic_network_forward": ([P, P, i64, P, P, P, sz, P, P, i32], ctypes.c_int),
         "bitlogic_network_forward_noalloc": ([P, P, i64, P, P, P], ctypes.c_int),
         "bitlogic_forward_grouped_dsp": ([P, i64, i32, P, i32, P, i32, i32, P, P, P, P, sz, P],
@@ -596,6 +598,15 @@ class BitlogicModel:
                 "head_planes": int(info.head_planes),
                 "jump_layers": [l for l in range(min(len(self.layers), 32))
                                 if (int(info.jump_layers) >> l) & 1]}
+
+    def path(self, n_samples: int) -> str:
+        """The kernels that forward() runs n_samples on: "slab", "columns" or
+        "block" (bitlogic_network_path)."""
+        net, keep = self._net()
+        path = ctypes.c_int32()
+        _check(load_library().bitlogic_network_path(ctypes.byref(net), n_samples,
+                                                    ctypes.byref(path)))
+        return _PATHS[path.value]
 
     def forward(self, x: torch.Tensor, out: Optional[torch.Tensor] = None,
                 argmax: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,

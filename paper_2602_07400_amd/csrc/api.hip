@@ -657,6 +657,20 @@ int bitlogic_network_plan(const bitlogic_network *net, int64_t n_samples,
     return ok();
 }
 
+int bitlogic_network_path(const bitlogic_network *net, int64_t n_samples, int32_t *path)
+{
+    if (!path)
+        return fail(BITLOGIC_ERR_NULL, "network_path: NULL path");
+    ForwardPlan fp;
+    int st = plan_network(net, n_samples, &fp);
+    if (st != BITLOGIC_OK)
+        return st;
+    *path = !fp.cols.ok ? BITLOGIC_PATH_SLAB
+            : fp.net.ok ? BITLOGIC_PATH_BLOCK
+                        : BITLOGIC_PATH_COLUMNS;
+    return ok();
+}
+
 int bitlogic_network_forward(const bitlogic_network *net, const uint8_t *x, int64_t n_samples,
                              int32_t *out, int32_t *argmax, void *workspace,
                              size_t workspace_bytes, void *stream, void *const *events,

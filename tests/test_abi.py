@@ -392,3 +392,33 @@ def test_probe_validation(lib):
     assert g(rows=FAKE + 8) == EALIGN
     assert g(sink=FAKE + 8) == EALIGN
     assert hbm(Wr, None, FAKE * 4, 0) == OK
+
+
+def _path(lib, n, d, b, specs, c, encoder=bl.ENCODER_THERMOMETER, dsp=False):
+    p, keep = _layers(specs)
+    net = bl._Network(d, encoder, b, FAKE, p, len(specs), c, int(dsp), FAKE, None)
+    path = ctypes.c_int32(-1)
+    assert lib.bitlogic_network_path(ctypes.byref(net), n, ctypes.byref(path)) == OK
+    return bl._PATHS[path.value]
+
+
+def test_network_path(lib, monkeypatch):
+    for v in ("BITLOGIC_JUMP_LAYER", "BITLOGIC_UNFUSED_HEAD"):
+        monkeypatch.delenv(v, raising=False)
+    tiny, paper = [(1000, 6)] * 2, [(4000, 4)] * 2
+    assert _path(lib, 4096, 784, 1, tiny, 10) == "block"
+    assert _path(lib, 1024, 784, 4, paper, 10) == "columns"
+    assert _path(lib, 1 << 18, 784, 4, paper, 10) == "slab"
+    assert _path(lib, 64, 784, 9, paper, 10) == "slab"           # no column encoder
+    assert _path(lib, 64, 784, 4, paper[:1], 10) == "slab"       # one layer
+    for switch in (("BITLOGIC_JUMP_LAYER", "0"), ("BITLOGIC_UNFUSED_HEAD", "1")):
+        monkeypatch.setenv(*switch)
+        assert _path(lib, 4096, 784, 1, tiny, 10) == "slab"
+        monkeypatch.delenv(switch[0])
+    p, keep = _layers(paper)
+    net = bl._Network(784, 0, 4, FAKE, p, 2, 10, 0, None, None)
+    assert lib.bitlogic_network_path(ctypes.byref(net), 64, None) == ENULL
+    path = ctypes.c_int32(-1)
+    net.n_classes = 7                                            # 4000 % 7 != 0
+    assert lib.bitlogic_network_path(ctypes.byref(net), 64, ctypes.byref(path)) == ESHAPE
+    assert path.value == -1

@@ -34,3 +34,23 @@ def test_algorithmic_work_of_c4():
     sp = bench.algorithmic(cfg, n, fused_head=True, fanin_hist=hist)
     assert sp["layer2"]["ops"] == 2 * 7 * 63000 * W + n * 64000 // 32
     assert sp["layer1"]["ops"] == st["layer1"]["ops"]
+
+
+def test_algorithmic_work_by_columns():
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2602_07400_amd.workloads import CONFIGS
+    cfg = CONFIGS["paper_mnist_w4000"]
+    n, out = 1024, 4 * 1024 * 10 + 4 * 1024
+    st = bench.algorithmic(cfg, n, True, path="slab")
+    # the last layer's kernel writes scores and argmax; nothing is left for the head
+    cols = bench.algorithmic(cfg, n, True, path="columns")
+    assert cols["layer2"]["bytes"] == st["layer2"]["bytes"] + out
+    assert cols["head"]["bytes"] == cols["head"]["ops"] == 0
+    # the quantized head reads the counts in a kernel of its own
+    dsp = bench.algorithmic(cfg, n, True, path="columns", dsp=True)
+    assert dsp["layer2"]["bytes"] == st["layer2"]["bytes"] + 4 * n * 10
+    assert dsp["head"]["bytes"] == 4 * n * 10 + out
+    one = bench.algorithmic(cfg, n, False, path="block")
+    assert list(one) == ["forward"] and one["forward"]["bytes"] == n * cfg.d + out
+    assert one["forward"]["ops"] == sum(v["ops"] for v in cols.values())
