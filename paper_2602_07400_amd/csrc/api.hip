@@ -154,12 +154,14 @@ bitlogic_network legacy_net(int32_t n_features, const uint8_t *thresholds, int32
 // 16.3 : 22.2 at 1.2M, 38.2 : 64.7 at 0.9M, but 32.0 : 30.2 at 3.5M, 45.9 :
 // 35.7 at 4.0M, 39.0 : 33.2 at 5.8M and 66.8 : 49.3 at 7.9M.
 constexpr int64_t kColumnMaxCost = 3000000;
-int64_t column_cost(int64_t W, int64_t wires, const bitlogic_layer *layers, int32_t L)
+bool columns_pay(int64_t W, int64_t wires, const bitlogic_layer *layers, int32_t L)
 {
+    // every sum stays below kColumnMaxCost + 5 * 2^31 and the product is not taken
+    // (sizes up to 2^40 samples and 2^31 rows a layer are planned for)
     int64_t per_column = wires;
-    for (int32_t l = 0; l < L; ++l)
+    for (int32_t l = 0; l < L && per_column <= kColumnMaxCost; ++l)
         per_column += (int64_t)layers[l].w_out * (layers[l].k <= 4 ? 2 : 5);
-    return W * per_column;
+    return W <= kColumnMaxCost / per_column;
 }
 
 int plan_forward(int64_t n, int32_t d, int32_t b, const bitlogic_layer *layers, int32_t L,
@@ -237,11 +239,10 @@ int plan_forward(int64_t n, int32_t d, int32_t b, const bitlogic_layer *layers, 
     // not receive over the encoded bits, which layer 0 has consumed by then.
     // Where a switch asks for other kernels, or the encoder has more wires a
     // feature than the column encoder's waves hold, the slab kernels run.
-    fp->cols = bl::plan_column_head(L >= 2 ? layers[L - 2].w_out : d * b, w_last, c);
-    fp->cols.ok = fp->cols.ok && L >= 2 && b <= 8 && fp->fused && jm == kJumpAuto &&
-                  (size_t)n * c * sizeof(int32_t) <= enc &&
-                  column_cost(fp->W, d * b, layers, L) <= kColumnMaxCost;
-    fp->net.ok = false;
+    fp->cols.ok = fp->net.ok = false;
+    if (L >= 2 && b <= 8 && fp->fused && jm == kJumpAuto &&
+        (size_t)n * c * sizeof(int32_t) <= enc && columns_pay(fp->W, d * b, layers, L))
+        fp->cols = bl::plan_column_head(layers[L - 2].w_out, w_last, c);
     if (fp->cols.ok && L <= bl::kColumnMaxLayers) {
         int32_t w[bl::kColumnMaxLayers], k[bl::kColumnMaxLayers];
         for (int32_t l = 0; l < L; ++l) {

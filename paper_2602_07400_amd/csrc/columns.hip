@@ -561,7 +561,7 @@ ColumnHeadPlan plan_column_head(int32_t w_in, int32_t w_out, int32_t c)
     p.cpb = (c + p.splits - 1) / p.splits;
     p.splits = (c + p.cpb - 1) / p.cpb;
     const size_t cnt = (size_t)p.cpb * kCntStride * 4 + 2 * kHeadWaves * kWave * 4;
-    const size_t rows = (size_t)(w_in + 1) / 2 * 16;
+    const size_t rows = ((size_t)w_in + 1) / 2 * 16;
     p.staged = cnt + rows <= kColumnLds;
     p.lds = cnt + (p.staged ? rows : 0);
     p.ok = p.lds <= kColumnLds;

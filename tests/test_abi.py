@@ -402,6 +402,17 @@ def _path(lib, n, d, b, specs, c, encoder=bl.ENCODER_THERMOMETER, dsp=False):
     return bl._PATHS[path.value]
 
 
+@pytest.mark.parametrize("n", [1 << 38, 1 << 39])
+def test_network_path_of_huge_shapes(lib, n, monkeypatch):
+    # a cost of 2^31 units a column, 2^63 and 2^64 in all, must not come out as
+    # a small one
+    for v in ("BITLOGIC_JUMP_LAYER", "BITLOGIC_UNFUSED_HEAD"):
+        monkeypatch.delenv(v, raising=False)
+    assert _path(lib, n, (1 << 30) - 2, 1, [((1 << 29) - 63, 4), (64, 1)], 2) == "slab"
+    # the most wires that are accepted, in a network of one layer
+    assert _path(lib, 64, (1 << 31) - 1, 1, [(64, 1)], 2) == "slab"
+
+
 def test_network_path(lib, monkeypatch):
     for v in ("BITLOGIC_JUMP_LAYER", "BITLOGIC_UNFUSED_HEAD"):
         monkeypatch.delenv(v, raising=False)
