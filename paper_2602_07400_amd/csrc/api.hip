@@ -154,6 +154,14 @@ bitlogic_network legacy_net(int32_t n_features, const uint8_t *thresholds, int32
 // 16.3 : 22.2 at 1.2M, 38.2 : 64.7 at 0.9M, but 32.0 : 30.2 at 3.5M, 45.9 :
 // 35.7 at 4.0M, 39.0 : 33.2 at 5.8M and 66.8 : 49.3 at 7.9M.
 constexpr int64_t kColumnMaxCost = 3000000;
+// The cost counts nodes, but a column's last kernel is a block of 1024 threads
+// however few of them it has: networks of 16 to 256 nodes a layer crossed at 1200
+// to 2000 columns far below that cost.  Stages by columns against slabs, 1024
+// columns: 16 -> 16 nodes 14.7 us : 16.8, 100 -> 100 14.7 : 17.7, 784 -> 100 ->
+// 100 26.1 : 27.2; 2048: 22.7 : 17.2, 23.8 : 22.5; 4096: 41 : 22, 43 : 33 (one
+// block a column, without a bound: 96 and 73).  k_col_encode's grid has a column
+// per block in y, of which there are at most 65535.
+constexpr int64_t kColumnMaxColumns = 1024;
 bool columns_pay(int64_t W, int64_t wires, const bitlogic_layer *layers, int32_t L)
 {
     // every sum stays below kColumnMaxCost + 5 * 2^31 and the product is not taken
@@ -161,7 +169,7 @@ bool columns_pay(int64_t W, int64_t wires, const bitlogic_layer *layers, int32_t
     int64_t per_column = wires;
     for (int32_t l = 0; l < L && per_column <= kColumnMaxCost; ++l)
         per_column += (int64_t)layers[l].w_out * (layers[l].k <= 4 ? 2 : 5);
-    return W <= kColumnMaxCost / per_column;
+    return W <= kColumnMaxColumns && W <= kColumnMaxCost / per_column;
 }
 
 int plan_forward(int64_t n, int32_t d, int32_t b, const bitlogic_layer *layers, int32_t L,

@@ -591,11 +591,18 @@ hipError_t launch_column_encode(const uint8_t *x, int64_t n, int32_t d, const ui
 // 2516 at fan-in 5 (16810) 14.3 against 13.2, 784 x 4 -> 4000 -> 4000 at fan-in 4
 // (20230) 15.8 against 13.1.
 constexpr int64_t kNetworkMaxWork = 14000;
+// The most columns: three rounds of blocks, one a CU, of 3 to 8 us each, or two
+// where rows are shorter than a group of features and are loaded a byte at a
+// time.  Against the stage kernels and the slab kernels at 512 columns 784 -> 100
+// -> 100 at fan-in 4 13.4 : 16.1 : 20.8 us, 32 -> 16 -> 16 14.1 : 12.1 : 14.7; at
+// 768 19.8 : 21.8 : 22.9 and 20.0 : 12.4 : 14.7; at 1024 26.6 : 26.1 : 27.2.
+constexpr int64_t kNetworkMaxColumns = 768;
+constexpr int64_t kNetworkMaxColumnsShortRows = 512;
 ColumnNetwork plan_column_network(int32_t d, int32_t b, const int32_t *w, const int32_t *k,
                                   int32_t n_layers, int32_t c, int64_t n)
 {
     ColumnNetwork net{};
-    if (n_layers > kColumnMaxLayers || n > (int64_t)kWave * 0x7fffffff)
+    if (n_layers > kColumnMaxLayers)
         return net;
     int32_t rows[2] = {d * b, 0};
     // wave instructions of a column: a group of 64 wires, 64 nodes, 64 nodes counted
@@ -615,7 +622,9 @@ ColumnNetwork plan_column_network(int32_t d, int32_t b, const int32_t *w, const 
     net.rows_b = rows[1];
     net.lds = ((size_t)rows[0] + rows[1]) * 8 + (size_t)c * kCntStride * 4 +
               2 * kHeadWaves * kWave * 4;
-    net.ok = net.lds <= kColumnLds && work <= kNetworkMaxWork;
+    const int64_t most = d < 4 * group_quads(b) ? kNetworkMaxColumnsShortRows
+                                                : kNetworkMaxColumns;
+    net.ok = net.lds <= kColumnLds && work <= kNetworkMaxWork && n <= kWave * most;
     return net;
 }
 

@@ -15,13 +15,15 @@ __device__ __forceinline__ uint32_t load_u32(const uint8_t *p)
     return v;
 }
 
+// Features per 64-wire group of b wires each, in quads whose four bytes are
+// compared at once: as many as fit, but one fewer at b = 3, so that a tile is a
+// whole number of 16-byte pieces and shares 128-byte pixel lines with its
+// neighbours instead of straddling them.
+constexpr int group_quads(int b) { return b == 3 ? 4 : 16 / b; }
+
 template <int B, int KG>
 struct EncGeom {
-    // Features per 64-wire group, in quads whose four bytes are compared at
-    // once; at B = 3 and 6 fewer quads than would fit, so that a tile is a
-    // whole number of 16-byte pieces and shares 128-byte pixel lines with its
-    // neighbours instead of straddling them.
-    static constexpr int kQ = (B == 3) ? 4 : 16 / B;     // quads per group
+    static constexpr int kQ = group_quads(B);            // quads per group
     static constexpr int kFPG = 4 * kQ;                  // features per group
     static constexpr int kS = kQ * B;                    // (quad, wire) slots per group
     static_assert(kS <= 16, "a group's wires fit one 64-bit row");

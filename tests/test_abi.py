@@ -402,6 +402,21 @@ def _path(lib, n, d, b, specs, c, encoder=bl.ENCODER_THERMOMETER, dsp=False):
     return bl._PATHS[path.value]
 
 
+def test_network_path_of_narrow_networks(lib, monkeypatch):
+    # a column takes a block of 1024 threads whatever it computes, so the number
+    # of columns is bounded however few nodes there are: one block a column up to
+    # 768 (512 where rows are shorter than a group of features), stages to 1024
+    for v in ("BITLOGIC_JUMP_LAYER", "BITLOGIC_UNFUSED_HEAD"):
+        monkeypatch.delenv(v, raising=False)
+    for d, b, specs, c, block in ((16, 8, [(64, 4)] * 2, 4, 768), (784, 1, [(100, 4)] * 2, 10, 768),
+                                  (32, 1, [(16, 4)] * 2, 1, 512), (4, 8, [(10, 6)] * 2, 1, 512),
+                                  (100, 4, [(200, 4)] * 5, 5, 0)):
+        for W in (1, 512, 513, 768, 769, 1024, 1025, 1 << 16):
+            want = "block" if W <= block else "columns" if W <= 1024 else "slab"
+            assert _path(lib, 64 * W, d, b, specs, c) == want, (d, W)
+            assert _path(lib, 64 * W - 63, d, b, specs, c) == want, (d, W)
+
+
 @pytest.mark.parametrize("n", [1 << 38, 1 << 39])
 def test_network_path_of_huge_shapes(lib, n, monkeypatch):
     # a cost of 2^31 units a column, 2^63 and 2^64 in all, must not come out as
