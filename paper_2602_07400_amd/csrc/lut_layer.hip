@@ -857,14 +857,14 @@ hipError_t launch_slab_head_k(const uint64_t *in, int32_t w_in, int64_t n_slabs,
 // kSlabWords words that take the place of the slabs.  The lines of a window lie
 // a row apart, so where a row is a large power of two they crowd into few sets
 // of the caches (32000 rows of 1024 words: 285 us, of 1040 words: 212).  Eight
-// lanes share a node at every fan-in: one load instruction then takes a whole
-// line, where two loads of half its pieces each found it evicted in between
-// (fan-in 5, 8000 -> 8000, W = 4096: four lanes 272 us, eight 193; fan-in 6,
-// 32000 -> 32000, W = 1024: 287, 235; rows that do not crowd, 9216 -> 32000 at
-// fan-in 6, W = 1040: 156, 169).  Loads and stores are 16 bytes at any 8-byte
-// address, so rows of an odd word count take no other path; stores are
-// non-temporal, as in the slab kernel; a ragged last window is part of the same
-// launch.  Against the kernel before (four lanes, plain stores, 8-byte accesses
+// lanes share a node: one load instruction then takes a whole line, where two
+// loads of half its pieces each found it evicted in between (fan-in 5, 8000 ->
+// 8000, W = 4096: four lanes 272 us, eight 193; fan-in 6, 32000 -> 32000, W =
+// 1024: 287, 235).  At fan-in 6 the reuse of a node's masks over 16 half-words
+// instead of 8 wins where the lines do stay (rows_stay below).  Loads and stores
+// are 16 bytes at any 8-byte address, so rows of an odd word count take no other
+// path; stores past the memory-side cache are non-temporal, as in the slab
+// kernel; a ragged last window is part of the same launch.  Against the kernel before (four lanes, plain stores, 8-byte accesses
 // for odd rows, the tail a launch of its own, 256-node blocks): 9216 -> 32000 at
 // fan-in 4, W = 1024 195 -> 101 us, 3920 -> 8011 at fan-in 4, W = 313 28.5 ->
 // 13.4, 9216 -> 32000 at fan-in 6, W = 1023 262 -> 206.
@@ -875,6 +875,27 @@ constexpr int kRowsLPN = 8;
 // (30000 -> 20000 at fan-in 5, W = 300, 2983 blocks of 128: 53.5 against 45.6).
 constexpr int kRowsNB = 128;
 constexpr int64_t kRowsSmallBlocks = 4096;
+// Whether a window's lines stay in the caches between two loads of half a line
+// each: rows of whole, aligned lines, an input of up to 90 MiB and, where a row is
+// a multiple of 8 KB, few enough rows for the sets that their lines share.
+// Fan-in 6, eight lanes against four (with 256-node blocks: 128 are up to 10%
+// slower): 3000 -> 8000 W = 256 14.2 : 12.6 us, W = 1024 47.8 : 41.4, 9216 -> 32000
+// W = 256 49.5 : 41.5, W = 1040 162 : 149, 32000 -> 32000 W = 256 52.7 : 47.9, 784
+// -> 1000 W = 4096 26.3 : 22.5; past the bounds 3000 -> 8000 W = 2048 82.8 : 88.5,
+// 9216 -> 32000 W = 1024 169 : 190 and W = 300 58.9 : 62.4, 32000 -> 32000 W = 640
+// 130 : 159.  At fan-in 5 eight are as fast or faster throughout.
+constexpr int kRowsFewLPN = 4;
+constexpr int kRowsFewNB = 256;
+constexpr int64_t kRowsStayBytes = (int64_t)90 << 20;
+constexpr int64_t kRowsShareWords = 1024;
+constexpr int64_t kRowsMaxShared = 6000000;
+bool rows_stay(const uint64_t *in, int32_t w_in, int64_t W)
+{
+    const int64_t power = W & -W;              // largest power of two in a row's words
+    return power >= kSlabWords && (uintptr_t)in % (kSlabWords * 8) == 0 &&
+           W <= kRowsStayBytes / 8 / w_in &&
+           (power < kRowsShareWords || w_in <= kRowsMaxShared / power);
+}
 
 template <int K, int LPN, int NB, bool NT>
 __global__ __launch_bounds__(kThreads) void k_lut_rows(
@@ -937,7 +958,7 @@ __global__ __launch_bounds__(kThreads) void k_lut_rows(
     }
 }
 
-template <int K, int NB>
+template <int K, int LPN, int NB>
 hipError_t launch_rows_kn(const uint64_t *in, int64_t W, const int32_t *conn,
                           const uint64_t *tables, int32_t w_out, uint64_t *out,
                           hipStream_t stream)
@@ -948,26 +969,38 @@ hipError_t launch_rows_kn(const uint64_t *in, int64_t W, const int32_t *conn,
     if (blocks > 0x7fffffff || n_win > 0x7fffffff)
         return hipErrorInvalidConfiguration;
     if (streams_past_cache((int64_t)w_out * W * 8))
-        hipLaunchKernelGGL((k_lut_rows<K, kRowsLPN, NB, true>), dim3((unsigned)blocks),
+        hipLaunchKernelGGL((k_lut_rows<K, LPN, NB, true>), dim3((unsigned)blocks),
                            dim3(kThreads), 0, stream, in, W, conn, tables, w_out, out, n_nblk,
                            (int32_t)n_win);
     else
-        hipLaunchKernelGGL((k_lut_rows<K, kRowsLPN, NB, false>), dim3((unsigned)blocks),
+        hipLaunchKernelGGL((k_lut_rows<K, LPN, NB, false>), dim3((unsigned)blocks),
                            dim3(kThreads), 0, stream, in, W, conn, tables, w_out, out, n_nblk,
                            (int32_t)n_win);
     return hipGetLastError();
 }
 
-template <int K>
-hipError_t launch_rows_k(const uint64_t *in, int64_t W, const int32_t *conn,
+// NB nodes a block, or one pass where that gives too few blocks.
+template <int K, int LPN, int NB>
+hipError_t launch_rows_l(const uint64_t *in, int64_t W, const int32_t *conn,
                          const uint64_t *tables, int32_t w_out, uint64_t *out,
                          hipStream_t stream)
 {
     const int64_t n_win = (W + kSlabWords - 1) / kSlabWords;
-    if (n_win * ((w_out + kRowsNB - 1) / kRowsNB) < kRowsSmallBlocks)
-        return launch_rows_kn<K, kThreads / kRowsLPN>(in, W, conn, tables, w_out, out,
+    if (n_win * ((w_out + NB - 1) / NB) < kRowsSmallBlocks)
+        return launch_rows_kn<K, LPN, kThreads / LPN>(in, W, conn, tables, w_out, out, stream);
+    return launch_rows_kn<K, LPN, NB>(in, W, conn, tables, w_out, out, stream);
+}
+
+template <int K>
+hipError_t launch_rows_k(const uint64_t *in, int32_t w_in, int64_t W, const int32_t *conn,
+                         const uint64_t *tables, int32_t w_out, uint64_t *out,
+                         hipStream_t stream)
+{
+    if constexpr (K == 6)
+        if (rows_stay(in, w_in, W))
+            return launch_rows_l<K, kRowsFewLPN, kRowsFewNB>(in, W, conn, tables, w_out, out,
                                                              stream);
-    return launch_rows_kn<K, kRowsNB>(in, W, conn, tables, w_out, out, stream);
+    return launch_rows_l<K, kRowsLPN, kRowsNB>(in, W, conn, tables, w_out, out, stream);
 }
 
 }  // namespace
@@ -1034,14 +1067,13 @@ hipError_t launch_lut_layer(const uint64_t *in, int32_t w_in, int64_t n_words,
                             int32_t w_out, int32_t k, uint64_t *out,
                             hipStream_t stream)
 {
-    (void)w_in;
     switch (k) {
-    case 1: return launch_rows_k<1>(in, n_words, conn, tables, w_out, out, stream);
-    case 2: return launch_rows_k<2>(in, n_words, conn, tables, w_out, out, stream);
-    case 3: return launch_rows_k<3>(in, n_words, conn, tables, w_out, out, stream);
-    case 4: return launch_rows_k<4>(in, n_words, conn, tables, w_out, out, stream);
-    case 5: return launch_rows_k<5>(in, n_words, conn, tables, w_out, out, stream);
-    case 6: return launch_rows_k<6>(in, n_words, conn, tables, w_out, out, stream);
+    case 1: return launch_rows_k<1>(in, w_in, n_words, conn, tables, w_out, out, stream);
+    case 2: return launch_rows_k<2>(in, w_in, n_words, conn, tables, w_out, out, stream);
+    case 3: return launch_rows_k<3>(in, w_in, n_words, conn, tables, w_out, out, stream);
+    case 4: return launch_rows_k<4>(in, w_in, n_words, conn, tables, w_out, out, stream);
+    case 5: return launch_rows_k<5>(in, w_in, n_words, conn, tables, w_out, out, stream);
+    case 6: return launch_rows_k<6>(in, w_in, n_words, conn, tables, w_out, out, stream);
     default: return hipErrorInvalidValue;
     }
 }

@@ -30,9 +30,14 @@ def run(w_in, w, k, W, shift, seed):
     src.copy_(torch.from_numpy(bits.view(np.int64)))
     out = bl.bitlogic_lut_layer(src, torch.from_numpy(conn).to(DEV),
                                 torch.from_numpy(tab.view(np.int64)).to(DEV), bits_out=dst)
-    v = np.unpackbits(bits.view(np.uint8), axis=1, bitorder="little").T
+    # every word, or of long rows the first and last windows and 32 others
+    cols = (np.arange(W) if W <= 64 else
+            np.r_[0:16, np.sort(rng.choice(np.arange(16, W - 16), 32, replace=False)), W - 16:W])
+    v = np.unpackbits(np.ascontiguousarray(bits[:, cols]).view(np.uint8), axis=1,
+                      bitorder="little").T
     want = oracle.lut_layer(np.ascontiguousarray(v), conn, tab)
-    got = np.unpackbits(out.cpu().numpy().view(np.uint8), axis=1, bitorder="little").T
+    got = out[:, torch.from_numpy(cols).to(DEV)].cpu().numpy()
+    got = np.unpackbits(got.view(np.uint8), axis=1, bitorder="little").T
     assert np.array_equal(got, want)
 
 
@@ -41,6 +46,21 @@ def run(w_in, w, k, W, shift, seed):
 def test_windows(k, W):
     run(50 + k, 131, k, W, W % 2, 10 * W + k)
     run(40, 32, k, W, 1, 10 * W + k + 1)
+
+
+@pytest.mark.parametrize("w_in,w,W,shift", [
+    (60, 70, 16, 0),                  # one window, nodes in a short pass
+    (60, 70, 48, 16),                 # buffers that start a line later
+    (60, 70, 48, 2),                  # and inside one
+    (300, 64 * 3 + 1, 1024, 0),       # a row of 8 KB
+    (5859, 70, 1024, 0),              # the most rows of it, and one more
+    (5860, 70, 1024, 0),
+    (300, 256 * 136 + 5, 480, 0),     # multi-pass blocks, the last of 5 nodes
+    (24000, 70, 480, 0),              # 88 and 92 MiB of input
+    (25200, 70, 480, 0),
+])
+def test_lanes_a_node_at_fan_in_6(w_in, w, W, shift):
+    run(w_in, w, 6, W, shift, w_in + W)
 
 
 @pytest.mark.parametrize("k", [1, 3, 4, 5, 6])
