@@ -33,6 +33,14 @@ def test_columns(n, d, groups):
     check(x, 1 + d % 8, groups, d % 3)
 
 
+@pytest.mark.parametrize("n", [19, 20, 21, 500, 511, 512, 513])
+@pytest.mark.parametrize("d,groups", [(784, 1), (3072, 3), (12, 4)])
+def test_few_rows(n, d, groups):
+    # 20, 5 or 1024 rows a block where the batch has fewer than 512 times as many
+    rng = np.random.default_rng(n * 3 + d)
+    check((rng.random((n, d)) ** 2 * 256).astype(np.uint8), 4, groups, 1)
+
+
 @pytest.mark.parametrize("value", [0, 255])
 def test_one_bin(value):
     check(np.full((600, 37), value, dtype=np.uint8), 3, 1, 1)
