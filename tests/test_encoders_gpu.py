@@ -16,6 +16,7 @@ import torch
 import oracle
 from paper_2602_07400_amd import bitlogic as bl
 from paper_2602_07400_amd.workloads import make_workload
+from paths import each_path
 
 pytestmark = pytest.mark.gpu
 
@@ -81,14 +82,15 @@ def test_fit_quantiles_collapse_and_mixture():
 
 def _net_check(wl, model, binary_bits=0, dsp=None):
     x = torch.from_numpy(wl.x).to(DEV)
-    out, am = model.forward(x)
-    torch.cuda.synchronize()
     th = None if binary_bits else model.thresholds.cpu().numpy()
     rs, rp = oracle.forward(wl.x, th, wl.layers, wl.n_classes, binary_bits=binary_bits)
     if dsp is not None:
         rs, rp = oracle.grouped_dsp(rs, dsp)
-    assert np.array_equal(out.cpu().numpy().astype(np.int64), rs.astype(np.int64))
-    assert np.array_equal(am.cpu().numpy(), rp)
+    with pytest.MonkeyPatch.context() as monkeypatch:
+        for path in each_path(monkeypatch, model, wl.n):
+            out, am = model.forward(x)
+            assert np.array_equal(out.cpu().numpy().astype(np.int64), rs.astype(np.int64)), path
+            assert np.array_equal(am.cpu().numpy(), rp), path
 
 
 @pytest.mark.parametrize("b,head", [(2, False), (8, False), (3, True)])

@@ -15,6 +15,7 @@ import torch
 import oracle
 from paper_2602_07400_amd import bitlogic as bl
 from paper_2602_07400_amd.workloads import make_workload
+from paths import each_path
 
 pytestmark = pytest.mark.gpu
 
@@ -55,14 +56,17 @@ def _replays(model, wl, ref_fn, n, seeds=(11, 12, 13)):
     del g
 
 
-@pytest.mark.parametrize("name,n", [("c1_mnist_tiny", 4096 + 37), ("c3_cifar10", 2000)])
-def test_graph_replay_groupsum(name, n):
+@pytest.mark.parametrize("name,n", [("c1_mnist_tiny", 4096 + 37), ("paper_mnist_w4000", 1000),
+                                    ("c3_cifar10", 2000)])
+def test_graph_replay_groupsum(name, n, monkeypatch):
     wl = make_workload(name, seed=21, n=n)
     model = bl.BitlogicModel.from_numpy(wl.thresholds, wl.layers, wl.n_classes, device=DEV)
-    _replays(model, wl, lambda xs: oracle.forward(xs, wl.thresholds, wl.layers, wl.n_classes), n)
+    for path in each_path(monkeypatch, model, n):
+        _replays(model, wl, lambda xs: oracle.forward(xs, wl.thresholds, wl.layers, wl.n_classes),
+                 n)
 
 
-def test_graph_replay_binary_encoder_quantized_head():
+def test_graph_replay_binary_encoder_quantized_head(monkeypatch):
     wl = make_workload("c1_mnist_tiny", seed=22, n=3000)
     d, b = wl.x.shape[1], 1
     rng = np.random.default_rng(5)
@@ -75,7 +79,8 @@ def test_graph_replay_binary_encoder_quantized_head():
         logits, pred = oracle.grouped_dsp(counts, q)
         return logits.astype(np.int32), pred
 
-    _replays(model, wl, ref, 3000)
+    for path in each_path(monkeypatch, model, 3000):
+        _replays(model, wl, ref, 3000)
 
 
 def test_graph_replay_specialized():

@@ -17,6 +17,7 @@ import torch
 import oracle
 from paper_2602_07400_amd import bitlogic as bl
 from paper_2602_07400_amd.workloads import CONFIG_ORDER, CONFIGS, make_workload
+from paths import each_path
 
 pytestmark = pytest.mark.gpu
 
@@ -241,17 +242,17 @@ def test_head_argmax_only_and_padding_ignored():
 def _check_forward(wl, idx=None):
     model = bl.BitlogicModel.from_numpy(wl.thresholds, wl.layers, wl.n_classes, device=DEV)
     x = torch.from_numpy(wl.x).to(DEV)
-    scores, argmax = model.forward(x)
-    torch.cuda.synchronize()
-    got_s, got_p = scores.cpu().numpy(), argmax.cpu().numpy()
     if idx is None:
         ref_s, ref_p = oracle.forward(wl.x, wl.thresholds, wl.layers, wl.n_classes)
         sel = slice(None)
     else:
         ref_s, ref_p = oracle.forward(wl.x[idx], wl.thresholds, wl.layers, wl.n_classes)
         sel = idx
-    assert np.array_equal(got_s[sel], ref_s), _report("scores", got_s[sel], ref_s)
-    assert np.array_equal(got_p[sel], ref_p), _report("argmax", got_p[sel], ref_p)
+    with pytest.MonkeyPatch.context() as monkeypatch:
+        for path in each_path(monkeypatch, model, wl.n):
+            got_s, got_p = (v.cpu().numpy() for v in model.forward(x))
+            assert np.array_equal(got_s[sel], ref_s), path + _report("scores", got_s[sel], ref_s)
+            assert np.array_equal(got_p[sel], ref_p), path + _report("argmax", got_p[sel], ref_p)
     return got_s, got_p
 
 
@@ -317,7 +318,7 @@ def test_forward_matches_staged_calls_and_is_deterministic():
     assert torch.equal(s1, s3) and torch.equal(p1, p3)
 
 
-def test_forward_single_layer_and_deep_stack():
+def test_forward_single_layer_and_deep_stack(monkeypatch):
     rng = np.random.default_rng(12)
     n, d, b = 1500, 50, 2
     x = rng.integers(0, 256, size=(n, d), dtype=np.uint8)
@@ -330,9 +331,10 @@ def test_forward_single_layer_and_deep_stack():
         w_in = w
     for L, c in ((1, 6), (5, 3)):
         m = bl.BitlogicModel.from_numpy(th, layers[:L], c, device=DEV)
-        s, p = m.forward(torch.from_numpy(x).to(DEV))
         rs, rp = oracle.forward(x, th, layers[:L], c)
-        assert np.array_equal(s.cpu().numpy(), rs) and np.array_equal(p.cpu().numpy(), rp)
+        for path in each_path(monkeypatch, m, n):
+            s, p = m.forward(torch.from_numpy(x).to(DEV))
+            assert np.array_equal(s.cpu().numpy(), rs) and np.array_equal(p.cpu().numpy(), rp), path
 
 
 def test_forward_on_side_stream():
@@ -396,12 +398,14 @@ def test_forward_fused_head_matches_oracle_and_unfused(g, c, k, n, monkeypatch):
         layers.append((conn, rng.integers(0, 1 << 63, size=w).astype(np.uint64)))
     m = bl.BitlogicModel.from_numpy(th, layers, c, device=DEV)
     xt = torch.from_numpy(x).to(DEV)
-    s_f, p_f = m.forward(xt)
-    monkeypatch.setenv("BITLOGIC_UNFUSED_HEAD", "1")
-    s_u, p_u = m.forward(xt)
-    monkeypatch.delenv("BITLOGIC_UNFUSED_HEAD")
     rs, rp = oracle.forward(x, th, layers, c)
-    assert np.array_equal(s_f.cpu().numpy(), rs) and np.array_equal(p_f.cpu().numpy(), rp)
+    for path in each_path(monkeypatch, m, n):
+        s_f, p_f = m.forward(xt)
+        assert np.array_equal(s_f.cpu().numpy(), rs) and np.array_equal(p_f.cpu().numpy(), rp), path
+    assert path == "slab" and m.plan(n)["fused_head"]
+    monkeypatch.setenv("BITLOGIC_UNFUSED_HEAD", "1")
+    assert m.path(n) == "slab" and not m.plan(n)["fused_head"]
+    s_u, p_u = m.forward(xt)
     assert torch.equal(s_f, s_u) and torch.equal(p_f, p_u)
 
 

@@ -6,7 +6,8 @@ code with 1..8 bits), depth 1..3, per-layer widths and fan-ins 1..6
 (connections with and without repeats, junk table bits above 2^k), class
 count and group size (1 node up to 1000 per class, fused and separate head),
 head (GroupSum or the quantized head) and table specialization, and compares
-scores (or logits) and argmax with the oracle on every sample.  The case
+scores (or logits) and argmax with the oracle on every sample, by columns and by
+slabs where the batch is small enough for columns.  The case
 parameters are printed before each run, so a failure names its shape.
 """
 import numpy as np
@@ -15,6 +16,7 @@ import torch
 
 import oracle
 from paper_2602_07400_amd import bitlogic as bl
+from paths import each_path
 
 DEV = torch.device("cuda:0")
 N_CASES = 160
@@ -75,7 +77,7 @@ def test_case_draws_are_valid():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("seed", range(N_CASES))
-def test_random_network(seed):
+def test_random_network(seed, monkeypatch):
     case = draw_case(seed)
     print("[case]", case, flush=True)
     x, th, layers, q = build(case)
@@ -84,12 +86,12 @@ def test_random_network(seed):
           else {})
     model = bl.BitlogicModel.from_numpy(th, layers, c, device=DEV, head_weights=q,
                                         specialize=0.0 if case["specialize"] else False, **kw)
-    s, p = model.forward(torch.from_numpy(x).to(DEV))
-    torch.cuda.synchronize()
     bits = case["b"] if case["binary"] else 0
     rs, rp = oracle.forward(x, th, layers, c, binary_bits=bits)
     if q is not None:
         rs, rp = oracle.grouped_dsp(rs, q)
-    s, p = s.cpu().numpy(), p.cpu().numpy()
-    bad = np.nonzero((s != rs).any(axis=1) | (p != rp))[0]
-    assert bad.size == 0, f"{bad.size} of {case['n']} samples differ, first {bad[:8]}"
+    xd = torch.from_numpy(x).to(DEV)
+    for path in each_path(monkeypatch, model, case["n"]):
+        s, p = (v.cpu().numpy() for v in model.forward(xd))
+        bad = np.nonzero((s != rs).any(axis=1) | (p != rp))[0]
+        assert bad.size == 0, f"{path}: {bad.size} of {case['n']} samples differ, first {bad[:8]}"

@@ -5,7 +5,8 @@ the host: nodes ordered by effective fan-in, each kernel pass evaluating its
 fan-in); the oracle runs the original network.  Every comparison is
 bit-exact: scores and argmax.  Cases: tied connections from small per-node
 pools, tables that ignore some of their inputs, constant and pass-through
-nodes, the fused and the unfused head, small-batch launches, both encoders,
+nodes, the fused and the unfused head, small-batch launches (by columns and by
+slabs), both encoders,
 both heads, ragged and single-sample batches, and the collapsed-routing
 CIFAR-100 workload at its full batch on sampled rows.
 """
@@ -16,6 +17,7 @@ import torch
 import oracle
 from paper_2602_07400_amd import bitlogic as bl
 from paper_2602_07400_amd.workloads import CONFIGS, make_workload
+from paths import each_path
 
 pytestmark = pytest.mark.gpu
 
@@ -54,17 +56,18 @@ def _check(x, th, layers, c, specialize, binary_bits=0, dsp=None, sample=None):
     if dsp is None and x.shape[0] > 0:
         plain = bl.BitlogicModel.from_numpy(th, layers, c, device=DEV, **kw)
         assert m.plan(x.shape[0])["fused_head"] == plain.plan(x.shape[0])["fused_head"]
-    s, p = m.forward(torch.from_numpy(x).to(DEV))
-    torch.cuda.synchronize()
-    s, p = s.cpu().numpy(), p.cpu().numpy()
     xs = x if sample is None else x[sample]
     if dsp is None:
         rs, rp = oracle.forward(xs, th, layers, c, binary_bits=binary_bits)
     else:
         rs, rp = _oracle_dsp(xs, th, layers, c, binary_bits, dsp)
     sel = slice(None) if sample is None else sample
-    assert np.array_equal(s[sel], rs)
-    assert np.array_equal(p[sel], rp)
+    xd = torch.from_numpy(x).to(DEV)
+    with pytest.MonkeyPatch.context() as monkeypatch:
+        for path in each_path(monkeypatch, m, x.shape[0]):
+            s, p = (v.cpu().numpy() for v in m.forward(xd))
+            assert np.array_equal(s[sel], rs), path
+            assert np.array_equal(p[sel], rp), path
     return m
 
 
