@@ -66,7 +66,9 @@ __host__ __device__ inline int64_t dealt_blocks(int64_t groups, int64_t parts)
 
 // The group and part of block bid of a dealt launch (of dealt_blocks blocks);
 // false for a block past the XCD's run.
-__device__ __forceinline__ bool dealt_task(int bid, int groups, int parts, int &group, int &part)
+__host__ __device__ inline __attribute__((always_inline)) bool dealt_task(int bid, int groups,
+                                                                        int parts, int &group,
+                                                                        int &part)
 {
     const int xcd = bid % kXcds, loc = bid / kXcds;
     const int rounds = groups / kXcds, rest = groups % kXcds * parts;
@@ -75,7 +77,7 @@ __device__ __forceinline__ bool dealt_task(int bid, int groups, int parts, int &
         part = loc % parts;
         return true;
     }
-    const int run = (rest + kXcds - 1) / kXcds;
+    const int run = (rest + (kXcds - 1)) / kXcds;
     const int e = xcd * run + loc - rounds * parts;
     group = rounds * kXcds + e / parts;
     part = e % parts;
