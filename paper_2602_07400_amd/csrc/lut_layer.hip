@@ -877,7 +877,9 @@ constexpr int kRowsNB = 128;
 constexpr int64_t kRowsSmallBlocks = 4096;
 // Whether a window's lines stay in the caches between two loads of half a line
 // each: rows of whole, aligned lines, an input of up to 90 MiB and, where a row is
-// a multiple of 8 KB, few enough rows for the sets that their lines share.
+// a multiple of 8 KB, few enough rows for the sets that their lines share; of
+// other rows, long ones of inputs of up to 16 MiB (35 -> 22000 at W = 6866, stored
+// through the L2, 798 us with eight lanes against 740).
 // Fan-in 6, eight lanes against four (with 256-node blocks: 128 are up to 10%
 // slower): 3000 -> 8000 W = 256 14.2 : 12.6 us, W = 1024 47.8 : 41.4, 9216 -> 32000
 // W = 256 49.5 : 41.5, W = 1040 162 : 149, 32000 -> 32000 W = 256 52.7 : 47.9, 784
@@ -887,13 +889,15 @@ constexpr int64_t kRowsSmallBlocks = 4096;
 constexpr int kRowsFewLPN = 4;
 constexpr int kRowsFewNB = 256;
 constexpr int64_t kRowsStayBytes = (int64_t)90 << 20;
+constexpr int64_t kRowsStaySplitBytes = (int64_t)16 << 20;
 constexpr int64_t kRowsShareWords = 1024;
 constexpr int64_t kRowsMaxShared = 6000000;
 bool rows_stay(const uint64_t *in, int32_t w_in, int64_t W)
 {
     const int64_t power = W & -W;              // largest power of two in a row's words
-    return power >= kSlabWords && (uintptr_t)in % (kSlabWords * 8) == 0 &&
-           W <= kRowsStayBytes / 8 / w_in &&
+    const bool lines = power >= kSlabWords && (uintptr_t)in % (kSlabWords * 8) == 0;
+    return (lines || W >= kRowsShareWords) &&
+           W <= (lines ? kRowsStayBytes : kRowsStaySplitBytes) / 8 / w_in &&
            (power < kRowsShareWords || w_in <= kRowsMaxShared / power);
 }
 
@@ -958,6 +962,18 @@ __global__ __launch_bounds__(kThreads) void k_lut_rows(
     }
 }
 
+// Whether every window of a row starts at a half line: the 128 bytes that a
+// window's lanes store are then two or fewer whole half lines each.  Rows at other
+// addresses are stored through the L2, which joins the parts of a line; stored
+// non-temporally they went to memory as parts: 35 -> 22000 at fan-in 2, W = 1563
+// 244 us against 72, W = 6866 994 against 672; 9216 -> 32000 at fan-in 4, W = 3001
+// 727 against 529.  From half lines on the streams win: 9216 -> 32000 at fan-in 4,
+// W = 3000 395 against 440, W = 3008 326 against 335.
+bool whole_half_lines(const uint64_t *out, int64_t W)
+{
+    return W % 8 == 0 && (uintptr_t)out % 64 == 0;
+}
+
 template <int K, int LPN, int NB>
 hipError_t launch_rows_kn(const uint64_t *in, int64_t W, const int32_t *conn,
                           const uint64_t *tables, int32_t w_out, uint64_t *out,
@@ -968,7 +984,7 @@ hipError_t launch_rows_kn(const uint64_t *in, int64_t W, const int32_t *conn,
     const int64_t blocks = dealt_blocks(n_win, n_nblk);
     if (blocks > 0x7fffffff || n_win > 0x7fffffff)
         return hipErrorInvalidConfiguration;
-    if (streams_past_cache((int64_t)w_out * W * 8))
+    if (streams_past_cache((int64_t)w_out * W * 8) && whole_half_lines(out, W))
         hipLaunchKernelGGL((k_lut_rows<K, LPN, NB, true>), dim3((unsigned)blocks),
                            dim3(kThreads), 0, stream, in, W, conn, tables, w_out, out, n_nblk,
                            (int32_t)n_win);

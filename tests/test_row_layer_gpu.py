@@ -58,9 +58,19 @@ def test_windows(k, W):
     (300, 256 * 136 + 5, 480, 0),     # multi-pass blocks, the last of 5 nodes
     (24000, 70, 480, 0),              # 88 and 92 MiB of input
     (25200, 70, 480, 0),
+    (2000, 70, 1030, 0),              # rows of parts of lines, 15.7 and 16.1 MiB
+    (2050, 70, 1030, 1),
 ])
 def test_lanes_a_node_at_fan_in_6(w_in, w, W, shift):
     run(w_in, w, 6, W, shift, w_in + W)
+
+
+@pytest.mark.parametrize("W,shift", [(1563, 0), (1564, 0), (1560, 0), (1560, 8), (1560, 1),
+                                     (1568, 0)])
+@pytest.mark.parametrize("k", [2, 6])
+def test_tensors_past_the_cache(k, W, shift):
+    # 173 MB of output, in parts of lines, half lines and whole lines
+    run(40, 13800, k, W, shift, W + k + shift)
 
 
 @pytest.mark.parametrize("k", [1, 3, 4, 5, 6])
