@@ -53,8 +53,9 @@
  *   outside [0, w_in) is undefined behaviour.  The Python binding checks
  *   them on the host when it builds a model.
  * - Packed bit buffers (bits_in, bits_out, bits) must be 8-byte aligned
- *   (16-byte alignment together with an even word count W lets the kernels
- *   use 16-byte accesses); the workspace must be 256-byte aligned.  Pixels,
+ *   (16-byte alignment together with an even word count W lets the encoder
+ *   store 16 bytes at a time; buffers of whole 128-byte lines with W a
+ *   multiple of 16 are the fastest for every kernel); the workspace must be 256-byte aligned.  Pixels,
  *   thresholds, connections, tables, scores and argmax need only their
  *   natural alignment.
  * - Buffers written by a call must not overlap any buffer it reads.
@@ -154,9 +155,9 @@ size_t bitlogic_forward_workspace_bytes(int64_t n_samples, int32_t n_features,
 
 /* How bitlogic_forward runs a network of this shape (host only, no HIP
  * call, nothing enqueued).  It describes the slab kernels; small batches (of
- * networks of two and more layers and up to 8 wires a feature, without an
- * environment switch set) run by 64-sample columns in the same workspace, with
- * the same results (bitlogic_network_path says which).  Fills *info and returns BITLOGIC_OK, or returns
+ * networks of two and more layers, up to 8 wires a feature and about 32 wires a
+ * class, without an environment switch set) run by 64-sample columns in the same
+ * workspace, with the same results (bitlogic_network_path says which).  Fills *info and returns BITLOGIC_OK, or returns
  * the status bitlogic_forward would return for these sizes and descriptors
  * (info untouched).  Device pointers in `layers` are not dereferenced. */
 typedef struct bitlogic_forward_info {
@@ -193,7 +194,8 @@ int bitlogic_forward(const uint8_t *x, int64_t n_samples, int32_t n_features,
 
 /* bitlogic_forward plus stage timing, for profiling: the same kernels on the
  * same stream (but for the smallest batches and networks, which bitlogic_forward
- * runs as one kernel and this one stage by stage), and hipEventRecord(events[i], stream) at every stage boundary:
+ * runs as one kernel and this one stage by stage), and
+ * hipEventRecord(events[i], stream) at every stage boundary:
  * events[0] before the encoder, events[1] after it, events[1 + l] after
  * layer l (l = 1..n_layers), events[n_layers + 2] after the head.
  * `events` is a host array of n_events = n_layers + 3 hipEvent_t handles

@@ -13,8 +13,8 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libbitlogic.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["encode.hip", "lut_layer.hip", "lut_jump.hip", "columns.hip", "head.hip", "fit.hip", "specialize.hip",
-           "probes.hip", "api.hip"]
+SOURCES = ["encode.hip", "lut_layer.hip", "lut_jump.hip", "columns.hip", "head.hip", "fit.hip",
+           "specialize.hip", "probes.hip", "api.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

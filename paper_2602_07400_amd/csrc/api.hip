@@ -244,9 +244,11 @@ int plan_forward(int64_t n, int32_t d, int32_t b, const bitlogic_layer *layers, 
     // small batches run by 64-sample columns, in the space of the slab layout's
     // tensors (a column tensor is never larger): the encoded bits and the
     // activations where the slab layout has them, counts that the caller does
-    // not receive over the encoded bits, which layer 0 has consumed by then.
-    // Where a switch asks for other kernels, or the encoder has more wires a
-    // feature than the column encoder's waves hold, the slab kernels run.
+    // not receive over the encoded bits, which layer 0 has consumed by then (room
+    // for them there, 32 wires a class in whole slabs, is asked of every batch,
+    // since the plan does not know the outputs).  Where a switch asks for other
+    // kernels, or the encoder has more wires a feature than the column encoder's
+    // waves hold, the slab kernels run.
     fp->cols.ok = fp->net.ok = false;
     if (L >= 2 && b <= 8 && fp->fused && jm == kJumpAuto &&
         (size_t)n * c * sizeof(int32_t) <= enc && columns_pay(fp->W, d * b, layers, L))

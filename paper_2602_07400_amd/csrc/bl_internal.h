@@ -39,6 +39,9 @@ constexpr int kLayoutSlab = 1;
 // only push the kernel's input out of the L2: 200000 x 784 through 8000 and 8000
 // (tensors of 137 and 200 MB) 342 -> 316 with the bound between the two, 342 with
 // it above both; 160000 x 3072 through 32000 and 32000 (640 MB) 919 against 931.
+// What it costs: pixels read again from the same cache are displaced (200000 x 784,
+// b = 4, the same batch over and over 53 -> 72 us a bitlogic_encode, new batches 86
+// either way; with a layer of 4000 nodes after it 170 -> 144 and 168 -> 141).
 constexpr int64_t kStreamBytes = (int64_t)160 << 20;
 inline bool streams_past_cache(int64_t bytes) { return bytes > kStreamBytes; }
 

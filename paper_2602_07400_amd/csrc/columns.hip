@@ -232,8 +232,8 @@ __device__ __forceinline__ void column_results(int32_t *s_cnt, int64_t col, int6
     }
 }
 
-// Adds the popcounts of a wave's 64 node words (lane = node base + lane, nodes
-// past n1 zero) to the counts of their classes.
+// Adds the popcounts of a wave's 64 node words (lane = node base + lane; lanes past
+// n1 hold any words, which the masks leave out) to the counts of their classes.
 __device__ __forceinline__ void count_nodes(uint32_t (&o)[2], int base, int n1, int g, int c0,
                                             const Transpose &tr, int32_t *s_cnt)
 {

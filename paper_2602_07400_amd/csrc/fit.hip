@@ -26,7 +26,7 @@
 // batches, 805 MB in three groups in 148 us with all three launches (163 with
 // 16 copies, dword columns and 1024 blocks of 256 threads), the global adds of
 // the histograms at small ones: one round of 1024-thread blocks instead of 1024
-// blocks took 25 MB from 38 to 21 us and 0.25 MB from 29 to 21; rows that are not
+// blocks took 25 MB from 38 to 21 us and 0.25 MB from 30 to 12; rows that are not
 // whole dwords no longer go a byte per load (100000 x 2001 74 -> 43 us).  Two rows
 // in flight a thread were as fast as 4 and 3-7% faster than 8.
 #include "bl_internal.h"

@@ -359,8 +359,8 @@ __global__ __launch_bounds__(kThreads, BL_LUT_MINWAVES) void k_lut_slab(
                 const int kmin = __builtin_amdgcn_readfirstlane(s_kp[kPasses]);
                 const int kmax = __builtin_amdgcn_readfirstlane(s_kp[kPasses + 1]);
                 if (kmin == kmax) {
-                    split_passes_kp<0, K, R, kPasses, kPassNodes, NT>(kmax, src, s_conn, s_tab, lnode,
-                                                                  S, dst);
+                    split_passes_kp<0, K, R, kPasses, kPassNodes, NT>(kmax, src, s_conn, s_tab,
+                                                                      lnode, S, dst);
                     return;
                 }
             } else {
