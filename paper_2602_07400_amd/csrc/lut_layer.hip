@@ -860,14 +860,15 @@ hipError_t launch_slab_head_k(const uint64_t *in, int32_t w_in, int64_t n_slabs,
 // lanes share a node: one load instruction then takes a whole line, where two
 // loads of half its pieces each found it evicted in between (fan-in 5, 8000 ->
 // 8000, W = 4096: four lanes 272 us, eight 193; fan-in 6, 32000 -> 32000, W =
-// 1024: 287, 235).  At fan-in 6 the reuse of a node's masks over 16 half-words
-// instead of 8 wins where the lines do stay (rows_stay below).  Loads and stores
-// are 16 bytes at any 8-byte address, so rows of an odd word count take no other
-// path; stores past the memory-side cache are non-temporal, as in the slab
-// kernel; a ragged last window is part of the same launch.  Against the kernel before (four lanes, plain stores, 8-byte accesses
-// for odd rows, the tail a launch of its own, 256-node blocks): 9216 -> 32000 at
-// fan-in 4, W = 1024 195 -> 101 us, 3920 -> 8011 at fan-in 4, W = 313 28.5 ->
-// 13.4, 9216 -> 32000 at fan-in 6, W = 1023 262 -> 206.
+// 1024: 287, 235).  At fan-in 6 the reuse of a node's masks over 8 half-words
+// instead of 4 wins where the lines do stay (rows_stay below).  Loads and stores are
+// 16 bytes at any 8-byte address, so rows of an odd word count take no other path;
+// stores past the memory-side cache are non-temporal, as in the slab kernel, where
+// rows are whole half lines; a ragged last window is part of the same launch.
+// Against the kernel before (four lanes, plain stores, 8-byte accesses for odd rows,
+// the tail a launch of its own, 256-node blocks): 9216 -> 32000 at fan-in 4, W =
+// 1024 195 -> 101 us, 3920 -> 8011 at fan-in 4, W = 313 28.5 -> 13.4, 9216 -> 32000
+// at fan-in 6, W = 1023 262 -> 206.
 constexpr int kRowsLPN = 8;
 // Nodes per block: 128 (4 passes) where that gives enough blocks, else one pass.
 // 256 and 512 were slower where lines crowd (8000 -> 8000 at fan-in 5, W = 4100:
