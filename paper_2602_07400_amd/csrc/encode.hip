@@ -343,8 +343,8 @@ __global__ __launch_bounds__(kThreads) void k_encode_ballot(
 }
 
 // Groups per tile: 32 to 64 features where the batch gives kEncBigBlocks blocks
-// of them; half of that below, for more blocks and a shorter chain in each
-// (16384 x 784 at b = 7 13.7 -> 9.1 us; a quarter: 10.6; at 4096 blocks the big
+// of them; half of that below (at b = 3 and b >= 5; one group at b <= 2 and two at
+// b = 4 are not halved), for more blocks and a shorter chain in each (16384 x 784 at b = 7 13.7 -> 9.1 us; a quarter: 10.6; at 4096 blocks the big
 // tiles win, 131072 x 784 at b = 7 43.8 against 46.4 us, and at 2^18 x 3072 368
 // against 420, since more blocks share each pixel line).
 constexpr int64_t kEncBigBlocks = 2048;

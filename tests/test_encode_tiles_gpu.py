@@ -13,8 +13,8 @@ from paper_2602_07400_amd import bitlogic as bl
 pytestmark = pytest.mark.gpu
 
 DEV = torch.device("cuda:0")
-# features of one tile at b wires per feature, in large launches (half of it,
-# or all at b <= 2, in small ones)
+# features of one tile at b wires per feature, in large launches (half of it in
+# small ones at b = 3 and b >= 5)
 TILE = {1: 64, 2: 32, 3: 64, 4: 32, 5: 48, 6: 32, 7: 32, 8: 32}
 
 
